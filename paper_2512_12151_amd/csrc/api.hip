@@ -168,7 +168,11 @@ bf_status problem_init(bf_context* c, bf_problem* pb, const bf_mesh_desc* m, int
   if (hflags) return flags_to_status(c, hflags);
   for (auto& e : pb->ev)
     if (!e) HIPCHK(c, hipEventCreate(&e));
-  if (!pb->host_sc) HIPCHK(c, hipHostMalloc((void**)&pb->host_sc, sizeof(PcgScalars), hipHostMallocDefault));
+  if (!pb->host_sc) {
+    static_assert(sizeof(PcgScalars) % sizeof(unsigned long long) == 0, "host_stat follows the scalars");
+    HIPCHK(c, hipHostMalloc((void**)&pb->host_sc, sizeof(PcgScalars) + 2 * sizeof(unsigned long long), hipHostMallocDefault));
+    pb->host_stat = reinterpret_cast<unsigned long long*>(pb->host_sc + 1);
+  }
   ALLOC(c, pb->scal, sizeof(PcgScalars));
   HIPCHK(c, hipMemsetAsync(pb->scal.p, 0, sizeof(PcgScalars), s));
   HIPCHK(c, hipStreamSynchronize(s));
@@ -362,6 +366,7 @@ bf_status bf_footprint_bytes(int32_t n_nodes, int32_t n_tets, int32_t n_constrai
   b += N * 4 * 8 + C * 16 + cap * 4 * 2;           // incidence, candidates, pattern
   b += cap * (72 + 36 + 4 + 4 + 8 + 4);            // FP64 blocks, FP32 scaled blocks, ucol, eslot, transpose index, lsrc
   b += N * (12 * (4 + kPRing) + 24 + 24 + 48 + 24);   // grad, bhat, r, q, the direction ring, x, L, L^-1, p out
+  if (pcg_fused_groups(n_nodes)) b += N * 24;      // the second r and q of the one-kernel iteration
   b += 1 << 20;                                    // partials, scalars, scan scratch, the SpMV slice plan
   b += 4 * (N / 64 + 1);
   *out = b;
@@ -599,9 +604,10 @@ bf_status size_constraint_buffers(bf_problem* pb, int n_pt, int n_ee) {
   ALLOC(c, pb->xs, 24LL * N4);   // FP64 solution
   ALLOC(c, pb->rd, 24LL * N4);   // FP64 residual (replacement, refinement)
   ALLOC(c, pb->rpart, 8LL * (kMaxSpmvParts + 8 + 6 * 256 + 8));
-  ALLOC(c, pb->r, 12LL * N4);
+  const long long two = pcg_fused_groups(N) ? 2 : 1;   // the one-kernel iteration alternates between two r and q
+  ALLOC(c, pb->r, 12LL * N4 * two);
   ALLOC(c, pb->pring, 12LL * N4 * kPRing);
-  ALLOC(c, pb->q, 12LL * N4);
+  ALLOC(c, pb->q, 12LL * N4 * two);
   for (DevBuf* b : {&pb->Lf, &pb->Linv, &pb->bhat, &pb->xs, &pb->rd, &pb->r, &pb->pring, &pb->q})
     HIPCHK(c, hipMemsetAsync(b->p, 0, b->bytes, s));
   HIPCHK(c, hipStreamSynchronize(s));
@@ -653,9 +659,47 @@ bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* o, double* p_out, 
   }
   int launched = 0, total_iters = 0, timed = 0, replacements = 0;
   bool assembly_checked = false;
+  // A one-kernel solve: kept kFusedAhead launches ahead of what the device has
+  // reported into pinned memory (every fourth launch, and its end), so that
+  // neither side waits and few launches follow the end.  Sets host_sc->iter.
+  constexpr int kFusedAhead = 12;
+  auto run_fused = [&](PcgSystem Sx, bool use_bf16) -> bf_status {
+    volatile unsigned long long* st = pb->host_stat;
+    st[0] = st[1] = 0;
+    Sx.hstat = pb->host_stat;
+    long long mine = 0, spins = 0;
+    for (;;) {
+      const unsigned long long w = st[0];
+      if (w & 0xffffffffu) {
+        if ((w & 0xffffffffu) == kEndAssembly) {
+          int hf = 0;
+          bf_status r0 = read_flags(pb, &hf);
+          return r0 != BF_OK ? r0 : flags_to_status(c, hf);
+        }
+        break;
+      }
+      if (mine - (long long)(w >> 32) < kFusedAhead) {
+        const bool t = launched < ntime;
+        launch_pcg_fused(Sx, use_bf16, (int)(mine & 1), s, t ? pb->tev[2 * launched] : nullptr,
+                         t ? pb->tev[2 * launched + 1] : nullptr);
+        if (mine == 0) HIPCHK(c, hipGetLastError());
+        ++launched;
+        ++mine;
+        spins = 0;
+      } else if ((++spins & 0xfff) == 0) {   // the device stays behind: is the stream still sound?
+        const hipError_t e = hipStreamQuery(s);
+        if (e != hipSuccess && e != hipErrorNotReady) HIPCHK(c, e);
+      }
+    }
+    pb->host_sc->iter = (int)st[1];
+    timed = std::max(timed, std::min(ntime, launched));
+    total_iters += pb->host_sc->iter;
+    return BF_OK;
+  };
   // Runs the solve set up on S to its device-side stop; the first poll also
   // checks the assembly's error flags.
   auto run_solve = [&](const PcgSystem& Sx, bool use_bf16) -> bf_status {
+    if (Sx.fused_nwg) return run_fused(Sx, use_bf16);
     int mine = 0;
     for (;;) {
       for (int k = 0; k < poll; ++k) {

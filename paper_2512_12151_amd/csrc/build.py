@@ -9,7 +9,7 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 PKG = os.path.dirname(HERE)
-SOURCES = ["scan.hip", "setup.hip", "contact.hip", "elastic.hip", "assemble.hip", "pcg.hip", "subproblem.hip", "ccd.hip", "activeset.hip", "timestep.hip", "api.hip",
+SOURCES = ["scan.hip", "setup.hip", "contact.hip", "elastic.hip", "assemble.hip", "pcg.hip", "pcg_fused.hip", "subproblem.hip", "ccd.hip", "activeset.hip", "timestep.hip", "api.hip",
            "server.hip"]
 # host rules (include/bfal_host.h): no HIP, built with the host compiler
 HOST_SOURCES = ["host_rules.cpp"]

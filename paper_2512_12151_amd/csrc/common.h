@@ -27,6 +27,25 @@ enum : int {
 constexpr int kWave = 64;          // CDNA wavefront width
 constexpr int kBlock = 256;        // default workgroup size (4 waves)
 
+// State of a one-kernel PCG solve between launches (pcg_fused.hip).
+enum : int { kNormal = 0, kTested = 1, kFresh = 2, kReplace = 3 };
+// How a one-kernel solve ended; the first two are the values of PcgScalars::done.
+enum : int { kEndConverged = 1, kEndMaxIter = 2, kEndBreakdown = 8, kEndAssembly = 16 };
+struct PcgCtl {
+  int k;             // iteration of the state
+  int mode;          // kNormal, kTested, kFresh or kReplace
+  int done;          // 0, or how the solve ended
+  int launches;      // launches so far
+  int verified;      // iteration of the last residual replacement (-1: none)
+  // the solve's parameters, carried along so that a launch finds all it needs in one place
+  int every, max_iter, replace_on;
+  int phase;         // k modulo every: 0 where |L r| is tested
+  int pad;
+  double rho_prev;   // r^T r of iteration k - 1
+  double rt_ref;     // |L r|^2 right after the last residual replacement (or |b|^2)
+  double tol_bb;     // tol^2 |b|^2
+};
+
 // Device-resident scalars of one PCG solve (see pcg.hip for who writes what).
 struct PcgScalars {
   // Control words first, grouped so that each PCG kernel reads its own in one
@@ -52,6 +71,7 @@ struct PcgScalars {
   double stat_viol;  // max_i max(0, -c_i)
   double rt_ref;     // |L r|^2 right after the last residual replacement (or |b|^2)
   float alpha_hist[8];   // alpha_j at j % kXBatch (written by workgroup 0 of the update kernel)
+  PcgCtl ctl[2];         // state of a one-kernel solve (pcg_fused.hip), by the parity of the launch
 };
 
 // x += alpha_j p_j is applied kXBatch iterations at a time (the update kernel
@@ -71,6 +91,11 @@ constexpr int kPartQQ = kPartRQ + kMaxSpmvParts;        // |H p|^2
 constexpr int kPartsPerSystem = 3 * kMaxVecParts + 3 * kMaxSpmvParts;
 
 constexpr int kSlice = 64;         // rows per slice of the sliced block storage (one wavefront)
+
+// One-kernel PCG (pcg_fused.hip): the largest system it takes, in slices (one
+// per workgroup).  Its partials are five doubles per slice, for two iterations.
+constexpr int kFusedMaxSlices = 512;
+static_assert(2 * kFusedMaxSlices * 5 <= kPartsPerSystem, "they fit the partials");
 
 // One symmetric block system of the PCG, H_hat = L^{-1} H L^{-T} with identity
 // diagonal blocks, in sliced storage (kSlice consecutive rows per slice, slot k
@@ -102,6 +127,12 @@ struct PcgSystem {
   PcgScalars* sc;
   int spmv_wg0, spmv_nwg;
   int vec_wg0, vec_nwg;
+  // one-kernel iteration (fused_nwg > 0): r, P and q then hold two buffers
+  // pstride apart, by the parity of the iteration
+  int fused_wg0, fused_nwg;
+  const float* bhat;
+  const int* aflags;             // the assembly's error flags, or null
+  unsigned long long* hstat;     // pinned host words: launches << 32 | end code, iteration of the end; or null
 };
 
 __host__ __device__ inline int div_up(long long a, long long b) { return (int)((a + b - 1) / b); }
@@ -315,6 +346,14 @@ void launch_pcg_iteration(const PcgSystem& S, bool bf16, hipStream_t s, hipEvent
 // lists them, wg_sys_spmv / wg_sys_vec map each workgroup to its system.
 void launch_pcg_iteration_batched(const PcgSystem* sys, const int* wg_sys_spmv, int nwg_spmv, const int* wg_sys_vec,
                                   int nwg_vec, bool bf16, hipStream_t s);
+// pcg_fused.hip: the iteration in one kernel.  Workgroups of a system (0: it
+// takes the two kernels), one launch, and one launch for several systems.
+// par alternates 0, 1, 0, ... over the launches of a solve (of a batch), from
+// either value.
+int pcg_fused_groups(int N);
+void launch_pcg_fused(const PcgSystem& S, bool bf16, int par, hipStream_t s, hipEvent_t t0 = nullptr,
+                      hipEvent_t t1 = nullptr);
+void launch_pcg_fused_batched(const PcgSystem* sys, const int* wg_sys, int nwg, int par, hipStream_t s);
 // x += the directions the update kernel has not applied yet (before x is read).
 void launch_pcg_flush(const PcgSystem& S, hipStream_t s);
 // p = L^{-T} x in FP64 and the stats (max |p|, max violation).

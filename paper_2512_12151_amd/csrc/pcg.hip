@@ -62,7 +62,7 @@
 // scalars (alpha, beta, convergence) are kept per system.
 #include <hip/hip_ext.h>
 
-#include "common.h"
+#include "pcg_device.h"
 
 namespace bfal {
 
@@ -210,30 +210,6 @@ __device__ inline double sum_parts(const double* __restrict__ part, int n) {
   double s = 0.0;
   for (int k = threadIdx.x; k < n; k += NT) s += part[k];
   return block_sum_all<NT>(s);
-}
-
-// Dispatch ids go round-robin over the 8 XCDs: give each XCD one contiguous
-// range of logical workgroups.
-__device__ inline int xcd_block(int b, int nb) { return (nb % 8 == 0) ? (b % 8) * (nb / 8) + b / 8 : b; }
-
-__device__ inline void load_block(const float* __restrict__ u, int j, float b[9]) {
-  const float* s = u + 9LL * j;
-#pragma unroll
-  for (int m = 0; m < 9; ++m) b[m] = s[m];
-}
-
-// BF16 block: 10 half-words in 5 words, element 2i in the low half of word i.
-__device__ inline void load_block(const uint32_t* __restrict__ u, int j, float b[9]) {
-  const uint32_t* s = u + 5LL * j;
-  uint32_t w[5];
-#pragma unroll
-  for (int m = 0; m < 5; ++m) w[m] = s[m];
-#pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    b[2 * m] = __uint_as_float(w[m] << 16);
-    b[2 * m + 1] = __uint_as_float(w[m] & 0xffff0000u);
-  }
-  b[8] = __uint_as_float(w[4] << 16);
 }
 
 // Vector entries of p_k at node c (AoS [N4][3]: one 12-byte load per node).
@@ -700,6 +676,20 @@ k_init_scalars(const double* __restrict__ bb_part, int nbb, PcgScalars* sc, doub
     sc->brk = 0;
     sc->xbase = 0;
     sc->done = (bb == 0.0) ? 1 : (max_iter <= 0 ? 2 : 0);
+    PcgCtl c;
+    c.k = 0;
+    c.mode = kFresh;
+    c.done = sc->done;
+    c.launches = 0;
+    c.verified = -1;
+    c.every = sc->check_every;
+    c.max_iter = max_iter;
+    c.replace_on = replace;
+    c.phase = c.pad = 0;
+    c.rho_prev = 0.0;
+    c.rt_ref = bb;
+    c.tol_bb = sc->tol2 * bb;
+    sc->ctl[0] = sc->ctl[1] = c;
   }
 }
 
@@ -735,32 +725,10 @@ k_residual64(PcgSystem S, const float* __restrict__ bhat, const double* __restri
   // with bhat == nullptr: rd = H_hat xd and no partials
   const int lb = xcd_block(blockIdx.x, gridDim.x);
   const int wave = threadIdx.x / kSlice, lane = threadIdx.x % kSlice;
-  const float* __restrict__ blk = static_cast<const float*>(S.blk);
   double rt = 0.0;
   for (int sl = lb * kSlicesPerGroup + wave; sl < S.nslices; sl += gridDim.x * kSlicesPerGroup) {
-    const int bu = S.sbu[sl], wu = (S.sbu[sl + 1] - bu) / kSlice;
-    const int bl = S.sbl[sl], wl = (S.sbl[sl + 1] - bl) / kSlice;
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-    for (int kk = 0; kk < wu; ++kk) {
-      const int e = bu + kk * kSlice + lane;
-      const int c = S.scol[e];
-      float b[9];
-      load_block(blk, e, b);
-      const double x0 = xd[3LL * c], x1 = xd[3LL * c + 1], x2 = xd[3LL * c + 2];
-      a0 += (double)b[0] * x0 + (double)b[1] * x1 + (double)b[2] * x2;
-      a1 += (double)b[3] * x0 + (double)b[4] * x1 + (double)b[5] * x2;
-      a2 += (double)b[6] * x0 + (double)b[7] * x1 + (double)b[8] * x2;
-    }
-    for (int kk = 0; kk < wl; ++kk) {
-      const int2 t = S.sent[bl + kk * kSlice + lane];
-      const int c = t.y;
-      float b[9];
-      load_block(blk, t.x, b);
-      const double x0 = xd[3LL * c], x1 = xd[3LL * c + 1], x2 = xd[3LL * c + 2];
-      a0 += (double)b[0] * x0 + (double)b[3] * x1 + (double)b[6] * x2;
-      a1 += (double)b[1] * x0 + (double)b[4] * x1 + (double)b[7] * x2;
-      a2 += (double)b[2] * x0 + (double)b[5] * x1 + (double)b[8] * x2;
-    }
+    double a0, a1, a2;
+    row_product64(S, sl, lane, xd, a0, a1, a2);
     const int row = sl * kSlice + lane;
     const long long o = 3LL * row;
     if (row < S.N && !bhat) {
@@ -768,18 +736,11 @@ k_residual64(PcgSystem S, const float* __restrict__ bhat, const double* __restri
       rd[o + 1] = xd[o + 1] + a1;
       rd[o + 2] = xd[o + 2] + a2;
     } else if (row < S.N) {
-      const double r0 = (double)bhat[o] - (xd[o] + a0);
-      const double r1 = (double)bhat[o + 1] - (xd[o + 1] + a1);
-      const double r2 = (double)bhat[o + 2] - (xd[o + 2] + a2);
+      double r0, r1, r2;
+      rt += row_residual64(S, row, bhat, xd, a0, a1, a2, r0, r1, r2);
       rd[o] = r0;
       rd[o + 1] = r1;
       rd[o + 2] = r2;
-      const float* L = S.Lf + row;   // SoA [6][N4]
-      const long long n4 = S.N4;
-      const double t0 = (double)L[0] * r0;
-      const double t1 = (double)L[n4] * r0 + (double)L[2 * n4] * r1;
-      const double t2 = (double)L[3 * n4] * r0 + (double)L[4 * n4] * r1 + (double)L[5 * n4] * r2;
-      rt += t0 * t0 + t1 * t1 + t2 * t2;
     }
   }
   const double s = block_sum_all<kSpmvBlock>(rt);
@@ -975,6 +936,7 @@ void launch_pcg_init(const PcgSystem& S, const float* bhat, const double* bb_par
 }
 
 void launch_pcg_flush(const PcgSystem& S, hipStream_t s) {
+  if (S.fused_nwg) return;   // the one-kernel iteration keeps x up to date
   hipLaunchKernelGGL(k_flush_x, dim3(S.vec_nwg), dim3(kVecBlock), 0, s, S);
   hipLaunchKernelGGL(k_flush_mark, dim3(1), dim3(64), 0, s, S.sc);
 }

@@ -1,0 +1,79 @@
+// Device helpers shared by the PCG kernels (pcg.hip, pcg_fused.hip).
+#pragma once
+
+#include "common.h"
+#include "wave_ops.h"
+
+namespace bfal {
+
+// Dispatch ids go round-robin over the 8 XCDs: give each XCD one contiguous
+// range of logical workgroups.
+__device__ inline int xcd_block(int b, int nb) { return (nb % 8 == 0) ? (b % 8) * (nb / 8) + b / 8 : b; }
+
+__device__ inline void load_block(const float* __restrict__ u, int j, float b[9]) {
+  const float* s = u + 9LL * j;
+#pragma unroll
+  for (int m = 0; m < 9; ++m) b[m] = s[m];
+}
+
+// BF16 block: 10 half-words in 5 words, element 2i in the low half of word i.
+__device__ inline void load_block(const uint32_t* __restrict__ u, int j, float b[9]) {
+  const uint32_t* s = u + 5LL * j;
+  uint32_t w[5];
+#pragma unroll
+  for (int m = 0; m < 5; ++m) w[m] = s[m];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    b[2 * m] = __uint_as_float(w[m] << 16);
+    b[2 * m + 1] = __uint_as_float(w[m] & 0xffff0000u);
+  }
+  b[8] = __uint_as_float(w[4] << 16);
+}
+
+// H_hat x for row `lane` of slice sl, off-diagonal part, the FP32 blocks
+// widened to FP64: the upper slots in order, then the lower ones.
+__device__ inline void row_product64(const PcgSystem& S, int sl, int lane, const double* __restrict__ xd, double& a0,
+                                     double& a1, double& a2) {
+  const float* __restrict__ blk = static_cast<const float*>(S.blk);
+  const int bu = S.sbu[sl], wu = (S.sbu[sl + 1] - bu) / kSlice;
+  const int bl = S.sbl[sl], wl = (S.sbl[sl + 1] - bl) / kSlice;
+  a0 = a1 = a2 = 0.0;
+  for (int kk = 0; kk < wu; ++kk) {
+    const int e = bu + kk * kSlice + lane;
+    const int c = S.scol[e];
+    float b[9];
+    load_block(blk, e, b);
+    const double x0 = xd[3LL * c], x1 = xd[3LL * c + 1], x2 = xd[3LL * c + 2];
+    a0 += (double)b[0] * x0 + (double)b[1] * x1 + (double)b[2] * x2;
+    a1 += (double)b[3] * x0 + (double)b[4] * x1 + (double)b[5] * x2;
+    a2 += (double)b[6] * x0 + (double)b[7] * x1 + (double)b[8] * x2;
+  }
+  for (int kk = 0; kk < wl; ++kk) {
+    const int2 t = S.sent[bl + kk * kSlice + lane];
+    const int c = t.y;
+    float b[9];
+    load_block(blk, t.x, b);
+    const double x0 = xd[3LL * c], x1 = xd[3LL * c + 1], x2 = xd[3LL * c + 2];
+    a0 += (double)b[0] * x0 + (double)b[3] * x1 + (double)b[6] * x2;
+    a1 += (double)b[1] * x0 + (double)b[4] * x1 + (double)b[7] * x2;
+    a2 += (double)b[2] * x0 + (double)b[5] * x1 + (double)b[8] * x2;
+  }
+}
+
+// b_hat - (x + a) of one row in FP64 and its |L rd|^2.
+__device__ inline double row_residual64(const PcgSystem& S, int row, const float* __restrict__ bhat,
+                                        const double* __restrict__ xd, double a0, double a1, double a2, double& r0,
+                                        double& r1, double& r2) {
+  const long long o = 3LL * row;
+  r0 = (double)bhat[o] - (xd[o] + a0);
+  r1 = (double)bhat[o + 1] - (xd[o + 1] + a1);
+  r2 = (double)bhat[o + 2] - (xd[o + 2] + a2);
+  const float* L = S.Lf + row;   // SoA [6][N4]
+  const long long n4 = S.N4;
+  const double t0 = (double)L[0] * r0;
+  const double t1 = (double)L[n4] * r0 + (double)L[2 * n4] * r1;
+  const double t2 = (double)L[3 * n4] * r0 + (double)L[4 * n4] * r1 + (double)L[5 * n4] * r2;
+  return t0 * t0 + t1 * t1 + t2 * t2;
+}
+
+}  // namespace bfal

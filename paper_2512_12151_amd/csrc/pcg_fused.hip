@@ -1,0 +1,456 @@
+// One-kernel PCG iteration for systems of up to kFusedMaxSlices slices, the
+// sizes at which the two-kernel iteration of pcg.hip spends its time in kernel
+// boundaries and in chains of dependent loads, not in bytes.
+//
+// alpha_k and beta_k are both known once p^T q, r^T q and q^T q of iteration k
+// are (|r - alpha q|^2 by its expansion, see pcg.hip), so an iteration needs
+// one grid-wide reduction.  The launch at state k = (r_k, p_k, q_k and their
+// sums) therefore does the whole of
+//   r_{k+1} = r_k - alpha q_k,  p_{k+1} = r_{k+1} + beta p_k,
+//   x += alpha p_k,  q_{k+1} = H_hat p_{k+1}
+// and the partial sums of the next one.  Where the product needs p_{k+1} of
+// another row it forms it from that row's r_k, q_k and p_k (the two FMAs the
+// row's owner applies, so every copy has the same bits): three gathered
+// vectors instead of one, which is cheap while the vectors sit in the caches
+// and buys a kernel boundary (about 5 us of a 15 us iteration at 3k to 25k
+// nodes).  r, p and q alternate between two buffers, because other workgroups
+// still read the old ones.
+//
+// A slice (64 rows) belongs to kSliceWaves wavefronts.  They take its pairs of upper
+// and lower slots in turn, up to kRoundPairs each per round, with every load
+// of the round in flight at once, and leave the products B p_c and B^T p_r in
+// LDS; then one thread per vector entry adds them in the slots' order, upper
+// before lower, which is the order of the one-wavefront SpMV: the same sums,
+// bit for bit, but two memory round trips deep instead of two per four slots.
+//
+// The residual replacement (pcg.hip) runs in the same kernel: the state's
+// mode says what a launch does, and no host round trip is needed.
+//   kNormal   test r_k, then the step above
+//   kTested   the same, r_k was tested already
+//   kFresh    r_k is given (the start, or just replaced): form p_k =
+//             r_k + beta p_{k-1} and q_k
+//   kReplace  r_k = b_hat - H_hat x in FP64 from the FP32 blocks
+// The state is double-buffered by the parity of the launch, which the host
+// toggles: a launch reads one copy and its workgroup 0 writes the other.
+// Launches after the end copy the state on and return.
+//
+// Measured (us of kernel time per iteration, two kernels against this one):
+// 250 nodes 9.1 -> 6.1, 2,880 nodes 14.7 -> 6.8, 24,565 nodes 15.8 -> 9.0.  A
+// launch of 7 us spends about 2.9 us outside its own code (dispatch, the drain
+// of its stores) and 1.7 us in loads that wait for loads: the state and the
+// slot offsets, then the indices, then the gathers, behind which the sums hide.
+#include <hip/hip_ext.h>
+
+#include <type_traits>
+
+#include "pcg_device.h"
+
+namespace bfal {
+
+namespace {
+
+constexpr int kSliceWaves = 4;                                   // wavefronts per slice and workgroup
+constexpr int kFusedBlock = kSliceWaves * kWave;
+constexpr int kRoundPairs = 2;                                   // slot pairs per wavefront and round
+constexpr int kRound = kSliceWaves * kRoundPairs;
+constexpr int kRow3 = 3 * kSlice;                                // vector entries of a slice
+constexpr int kRecPerLane = kFusedMaxSlices / kWave;             // partials per lane of a sum
+static_assert(kFusedMaxSlices % kWave == 0 && kRow3 == 3 * kWave, "wavefronts 0-2 own the entries, 3 the norms");
+
+// Loads at a 32-bit byte offset from a uniform base: one address register each
+// instead of two (system_of admits a system only if they reach every array).
+struct F3 { float v[3]; };
+struct F9 { float v[9]; };
+struct U5 { uint32_t v[5]; };
+
+template <class T>
+__device__ __forceinline__ T at32(const void* __restrict__ base, unsigned byte) {
+  return *reinterpret_cast<const T*>(static_cast<const char*>(base) + byte);
+}
+
+template <class T>
+__device__ __forceinline__ void put32(T* __restrict__ base, unsigned byte, T v) {
+  *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + byte) = v;
+}
+
+__device__ __forceinline__ void load_block32(const float* __restrict__ base, unsigned slot, float b[9]) {
+  const F9 w = at32<F9>(base, 36u * slot);
+#pragma unroll
+  for (int m = 0; m < 9; ++m) b[m] = w.v[m];
+}
+
+__device__ __forceinline__ void load_block32(const uint32_t* __restrict__ base, unsigned slot, float b[9]) {
+  const U5 w = at32<U5>(base, 20u * slot);
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    b[2 * m] = __uint_as_float(w.v[m] << 16);
+    b[2 * m + 1] = __uint_as_float(w.v[m] & 0xffff0000u);
+  }
+  b[8] = __uint_as_float(w.v[4] << 16);
+}
+
+// A value that no workgroup of the launch writes, loaded through the scalar cache.
+template <class T>
+__device__ __forceinline__ T uniform_load(const T* p) {
+  static_assert(sizeof(T) % 4 == 0 && std::is_trivially_copyable<T>::value, "whole words");
+  const auto* w = (const __attribute__((address_space(4))) uint32_t*)(p);
+  uint32_t u[sizeof(T) / 4];
+#pragma unroll
+  for (unsigned m = 0; m < sizeof(T) / 4; ++m) u[m] = w[m];
+  T v;
+  __builtin_memcpy(&v, u, sizeof(T));
+  return v;
+}
+
+// Partial sum m (r^T r, |L r|^2, p^T q, r^T q, q^T q) of state k, one per workgroup.
+__device__ __forceinline__ double* record(const PcgSystem& S, int k, int m) {
+  return S.part + ((k & 1) * 5 + m) * kFusedMaxSlices;
+}
+
+// The launch's report to the host (pinned memory): launches made and, once
+// the solve has ended, the end's code and the iteration it ended at.
+__device__ __forceinline__ void report(const PcgSystem& S, int launches, int done, int k) {
+  if (!S.hstat || (!done && (launches & 3))) return;
+  if (done) {
+    __hip_atomic_store(&S.hstat[1], (unsigned long long)(unsigned)k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __threadfence_system();
+  }
+  __hip_atomic_store(&S.hstat[0], ((unsigned long long)(unsigned)launches << 32) | (unsigned)done, __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The next launch's state; with an end code also the solver's scalars.
+__device__ __forceinline__ void hand_on(const PcgSystem& S, PcgCtl next, int par) {
+  ++next.launches;
+  S.sc->ctl[par ^ 1] = next;
+  S.sc->iter = S.sc->xbase = next.k;   // x holds every direction so far
+  if (next.done == kEndBreakdown) {
+    S.sc->flags |= FLAG_BREAKDOWN;
+    S.sc->brk = 1;
+  } else if (next.done) {
+    S.sc->done = next.done;
+  }
+  report(S, next.launches, next.done, next.k);
+}
+
+// kReplace: r_k = b_hat - H_hat x in FP64 for the workgroup's slice (by one
+// wavefront, in k_residual64's order), rounded to FP32, with r^T r and |L r|^2.
+__device__ __forceinline__ void replace_residual(const PcgSystem& S, PcgCtl c, int sl, int par) {
+  const int t = threadIdx.x;
+  if (t >= kWave) return;
+  double a0, a1, a2, rr = 0.0, rt = 0.0;
+  row_product64(S, sl, t, S.x, a0, a1, a2);
+  const int row = sl * kSlice + t;
+  if (row < S.N) {
+    double r0, r1, r2;
+    rt = row_residual64(S, row, S.bhat, S.x, a0, a1, a2, r0, r1, r2);
+    float* r = S.r + (c.k & 1) * S.pstride + 3LL * row;
+    const float f0 = (float)r0, f1 = (float)r1, f2 = (float)r2;
+    r[0] = f0;
+    r[1] = f1;
+    r[2] = f2;
+    rr = (double)f0 * f0 + (double)f1 * f1 + (double)f2 * f2;
+  }
+  rr = wave_sum_all(rr);
+  rt = wave_sum_all(rt);
+  if (t == 0) {
+    record(S, c.k, 0)[sl] = rr;
+    record(S, c.k, 1)[sl] = rt;
+    if (sl == 0) {
+      c.mode = kFresh;
+      hand_on(S, c, par);
+    }
+  }
+}
+
+template <class BT>
+struct Slice {   // what a launch knows of its slice before the state
+  int bu, bl, wu, wl, w;
+  int uc[kRoundPairs], ub[kRoundPairs], lc[kRoundPairs];
+
+  __device__ __forceinline__ void load_indices(const PcgSystem& S, int kk0, int lane) {
+#pragma unroll
+    for (int j = 0; j < kRoundPairs; ++j) {
+      // past a width the last slot is read again (a slice without slots reads
+      // the next slice's, or the arrays' padding) and its product is not added
+      const int kk = kk0 + kSliceWaves * j;
+      uc[j] = at32<int>(S.scol + bu, 4u * (unsigned)(max(min(kk, wu - 1), 0) * kSlice + lane));
+      const int2 q = at32<int2>(S.sent + bl, 8u * (unsigned)(max(min(kk, wl - 1), 0) * kSlice + lane));
+      ub[j] = q.x;
+      lc[j] = q.y;
+    }
+  }
+};
+
+// One launch at a state to step from (kFreshState: to start or resume from).
+template <class BT, bool kFreshState>
+__device__ __forceinline__ void iterate(const PcgSystem& S, const PcgCtl& c, Slice<BT>& sl, int s, int par) {
+  __shared__ float prod[2][kRound][2][kRow3];
+  __shared__ float rsh[kRow3];
+  __shared__ double sums[5], tail[kSliceWaves][5];
+  const int t = threadIdx.x, lane = t % kWave, wv = __builtin_amdgcn_readfirstlane(t / kWave);
+  const int k = c.k, ko = kFreshState ? k : k + 1;   // ko: iteration of the outputs
+  // vectors: at a fresh state p_k = fma(beta, p_{k-1}, r_k), r_k stays; at k = 0 beta = 0 and r stands in for p
+  const float* __restrict__ rin = S.r + (k & 1) * S.pstride;
+  const float* __restrict__ qin = S.q + (k & 1) * S.pstride;
+  const float* __restrict__ pin = kFreshState && k == 0 ? rin : S.P + ((ko + 1) & 1) * S.pstride;
+  // partial sums of state k: wavefront 0 takes r^T r, 1 to 3 p^T q, r^T q and
+  // q^T q; |L r|^2, on iterations that test it, also wavefront 0
+  const bool test = kFreshState ? k > 0 : c.mode == kNormal && k > 0;
+  const bool check = kFreshState ? test : test && c.phase == 0;   // |L r|^2 of state k is there
+  const int nrec = S.fused_nwg;
+  double rec[kRecPerLane], rec1[kRecPerLane];
+  {
+    const double* __restrict__ a = record(S, k, wv == 0 ? 0 : wv + 1);
+    const double* __restrict__ b = wv == 0 ? record(S, k, 1) : a;   // (unconditional: see Slice)
+#pragma unroll
+    for (int u = 0; u < kRecPerLane; ++u) rec[u] = a[min(lane + u * kWave, nrec - 1)];
+#pragma unroll
+    for (int u = 0; u < kRecPerLane; ++u) rec1[u] = b[min(lane + u * kWave, nrec - 1)];
+  }
+  // this thread's own entry (threads 0..191: entry t of the slice)
+  const int n3 = 3 * S.N, el = kRow3 * s + t;
+  const bool own = t < kRow3 && el < n3;
+  const unsigned eo = 4u * min(el, n3 - 1);
+  const float r_o = at32<float>(rin, eo), p_o = at32<float>(pin, eo);
+  const float q_o = kFreshState ? 0.f : at32<float>(qin, eo);
+  const double x_o = kFreshState ? 0.0 : at32<double>(S.x, 2u * eo);
+  const int row = s * kSlice + lane;
+  float lf[6];   // for wavefront 3, where |L r|^2 of the output is wanted (unconditional: see Slice)
+  if (!kFreshState)
+#pragma unroll
+    for (int m = 0; m < 6; ++m) lf[m] = at32<float>(S.Lf, 4u * (m * S.N4 + min(row, S.N - 1)));
+  // a round's blocks and gathers, all in flight together
+  float bu_[kRoundPairs][9], bl_[kRoundPairs][9];
+  F3 ru[kRoundPairs], qu[kRoundPairs], pu[kRoundPairs], rl[kRoundPairs], ql[kRoundPairs], pl[kRoundPairs];
+  auto load_round = [&](int k0) {
+#pragma unroll
+    for (int j = 0; j < kRoundPairs; ++j) {
+      const int kk = k0 + wv + kSliceWaves * j;
+      load_block32(static_cast<const BT*>(S.blk), sl.bu + max(min(kk, sl.wu - 1), 0) * kSlice + lane, bu_[j]);
+      const unsigned o = 12u * sl.uc[j], ol = 12u * sl.lc[j];
+      ru[j] = at32<F3>(rin, o);
+      if (!kFreshState) qu[j] = at32<F3>(qin, o);
+      pu[j] = at32<F3>(pin, o);
+      load_block32(static_cast<const BT*>(S.blk), sl.ub[j], bl_[j]);
+      rl[j] = at32<F3>(rin, ol);
+      if (!kFreshState) ql[j] = at32<F3>(qin, ol);
+      pl[j] = at32<F3>(pin, ol);
+    }
+  };
+  load_round(0);
+  if (sl.w > kRound) sl.load_indices(S, kRound + wv, lane);
+  // the sums of state k, and what to do with it, while the loads are in flight
+  {
+    double v = 0.0;
+#pragma unroll
+    for (int u = 0; u < kRecPerLane; ++u) v += lane + u * kWave < nrec ? rec[u] : 0.0;
+    v = wave_sum_all(v);
+    if (lane == 0) sums[wv == 0 ? 0 : wv + 1] = v;
+    if (wv == 0 && check) {
+      v = 0.0;
+#pragma unroll
+      for (int u = 0; u < kRecPerLane; ++u) v += lane + u * kWave < nrec ? rec1[u] : 0.0;
+      v = wave_sum_all(v);
+      if (lane == 0) sums[1] = v;
+    }
+  }
+  __syncthreads();
+  const bool leader = s == 0 && t == kRow3;   // in the wavefront with the least to do
+  const double rho = sums[0], rt = check ? sums[1] : 0.0;
+  PcgCtl next = c;
+  float alpha = 0.f, beta = 0.f;
+  if (kFreshState) {
+    // a residual just replaced counts for convergence now
+    const bool converged = test && ((c.phase == 0 && rt <= c.tol_bb) || rho == 0.0);
+    if (k == 0 && S.aflags && *S.aflags) next.done = kEndAssembly;
+    else if (converged) next.done = kEndConverged;
+    else if (test && k >= c.max_iter) next.done = kEndMaxIter;
+    if (leader && test) {
+      S.sc->rho = rho;
+      S.sc->rr_true = rt;
+    }
+    if (next.done) {
+      if (leader) hand_on(S, next, par);
+      return;
+    }
+    if (k > 0) {
+      beta = c.rho_prev > 0.0 ? (float)(rho / c.rho_prev) : 0.f;
+      next.rt_ref = rt;
+      next.verified = k;
+    }
+    next.mode = kTested;
+  } else {
+    const double pq = sums[2], rq = sums[3], qq = sums[4];
+    const bool converged = test && ((check && rt <= c.tol_bb) || rho == 0.0);
+    const bool replace = test && c.replace_on && rho != 0.0 &&
+                         (converged ? c.verified != k : check && rt <= 1e-2 * c.rt_ref);
+    const bool capped = test && k >= c.max_iter;
+    const bool broken = !(pq > 0.0);
+    if (leader && test) {
+      S.sc->rho = rho;
+      if (check) S.sc->rr_true = rt;
+    }
+    if (__builtin_expect(replace | converged | capped | broken, 0)) {
+      if (replace) next.mode = kReplace;
+      else next.done = converged ? kEndConverged : capped ? kEndMaxIter : kEndBreakdown;
+      if (leader) hand_on(S, next, par);
+      return;
+    }
+    alpha = (float)(rho / pq);
+    const double ad = alpha;
+    const double rho_next = rho - 2.0 * ad * rq + ad * ad * qq;
+    beta = rho_next > 0.0 ? (float)(rho_next / rho) : 0.f;
+    next.k = k + 1;
+    next.phase = c.phase + 1 == c.every ? 0 : c.phase + 1;
+    next.mode = kNormal;
+    next.rho_prev = rho;
+  }
+  const bool norm = !kFreshState && next.phase == 0;   // |L r|^2 of the output state is wanted
+  const float r_n = kFreshState ? r_o : __fmaf_rn(-alpha, q_o, r_o);
+  const float s_n = __fmaf_rn(beta, p_o, r_n);
+  if (norm && t < kRow3) rsh[t] = r_n;
+  float acc = 0.f;
+  for (int k0 = 0, h = 0;; k0 += kRound, h ^= 1) {
+#pragma unroll
+    for (int j = 0; j < kRoundPairs; ++j) {
+      float p[3];
+#pragma unroll
+      for (int m = 0; m < 3; ++m)
+        p[m] = __fmaf_rn(beta, pu[j].v[m], kFreshState ? ru[j].v[m] : __fmaf_rn(-alpha, qu[j].v[m], ru[j].v[m]));
+      float* o = &prod[h][wv + kSliceWaves * j][0][3 * lane];
+#pragma unroll
+      for (int m = 0; m < 3; ++m)
+        o[m] = __fmaf_rn(bu_[j][3 * m + 2], p[2], __fmaf_rn(bu_[j][3 * m], p[0], __fmul_rn(bu_[j][3 * m + 1], p[1])));
+#pragma unroll
+      for (int m = 0; m < 3; ++m)
+        p[m] = __fmaf_rn(beta, pl[j].v[m], kFreshState ? rl[j].v[m] : __fmaf_rn(-alpha, ql[j].v[m], rl[j].v[m]));
+      o = &prod[h][wv + kSliceWaves * j][1][3 * lane];
+#pragma unroll
+      for (int m = 0; m < 3; ++m)
+        o[m] = __fmaf_rn(bl_[j][6 + m], p[2], __fmaf_rn(bl_[j][m], p[0], __fmul_rn(bl_[j][3 + m], p[1])));
+    }
+    const bool more = k0 + kRound < sl.w;
+    if (more) {   // the next round's loads pass behind the barrier and the sums
+      load_round(k0 + kRound);
+      if (k0 + 2 * kRound < sl.w) sl.load_indices(S, k0 + 2 * kRound + wv, lane);
+    }
+    __syncthreads();
+    if (t < kRow3) {
+      float y[kRound], z[kRound];
+#pragma unroll
+      for (int m = 0; m < kRound; ++m) {
+        y[m] = prod[h][m][0][t];
+        z[m] = prod[h][m][1][t];
+      }
+#pragma unroll
+      for (int m = 0; m < kRound; ++m) {
+        acc = k0 + m < sl.wu ? __fadd_rn(acc, y[m]) : acc;
+        acc = k0 + m < sl.wl ? __fadd_rn(acc, z[m]) : acc;
+      }
+    }
+    if (!more) break;
+  }
+  if (wv < 3) {
+    const float q_n = __fadd_rn(s_n, acc);
+    if (own) {
+      put32(S.q + (ko & 1) * S.pstride, eo, q_n);
+      put32(S.P + (ko & 1) * S.pstride, eo, s_n);
+      if (!kFreshState) {
+        put32(S.r + (ko & 1) * S.pstride, eo, r_n);
+        put32(S.x, 2u * eo, fma((double)alpha, (double)p_o, x_o));
+      }
+    }
+    const double rd = own ? (double)r_n : 0.0, sd = own ? (double)s_n : 0.0, qd = own ? (double)q_n : 0.0;
+    const double o0 = wave_sum_all(rd * rd), o2 = wave_sum_all(sd * qd), o3 = wave_sum_all(rd * qd),
+                 o4 = wave_sum_all(qd * qd);
+    if (lane == 0) {
+      tail[wv][0] = o0;
+      tail[wv][2] = o2;
+      tail[wv][3] = o3;
+      tail[wv][4] = o4;
+    }
+  } else if (norm) {
+    const float r0 = rsh[3 * lane], r1 = rsh[3 * lane + 1], r2 = rsh[3 * lane + 2];
+    const double t0 = (double)lf[0] * r0;
+    const double t1 = (double)lf[1] * r0 + (double)lf[2] * r1;
+    const double t2 = (double)lf[3] * r0 + (double)lf[4] * r1 + (double)lf[5] * r2;
+    const double o1 = wave_sum_all(row < S.N ? t0 * t0 + t1 * t1 + t2 * t2 : 0.0);
+    if (lane == 0) tail[0][1] = o1;
+  }
+  __syncthreads();
+  if (t < 5) record(S, ko, t)[s] = t == 1 ? (norm ? tail[0][1] : 0.0) : tail[0][t] + tail[1][t] + tail[2][t];
+  if (leader) hand_on(S, next, par);
+}
+
+template <class BT>
+__device__ __forceinline__ void fused_launch(const PcgSystem& S, int s, int par) {
+  // everything that does not depend on the state is asked for beside it
+  const PcgCtl c = uniform_load(&S.sc->ctl[par]);
+  Slice<BT> sl;
+  sl.bu = uniform_load(S.sbu + s);
+  sl.bl = uniform_load(S.sbl + s);
+  sl.wu = (uniform_load(S.sbu + s + 1) - sl.bu) / kSlice;
+  sl.wl = (uniform_load(S.sbl + s + 1) - sl.bl) / kSlice;
+  sl.w = max(sl.wu, sl.wl);
+  sl.load_indices(S, __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), threadIdx.x % kWave);
+  if (__builtin_expect((c.done != 0) | (c.mode > kTested), 0)) {
+    if (c.done) {   // ended: hand the state on
+      if (s == 0 && threadIdx.x == 0) {
+        PcgCtl next = c;
+        ++next.launches;
+        S.sc->ctl[par ^ 1] = next;
+        report(S, next.launches, c.done, c.k);
+      }
+    } else if (c.mode == kFresh) {
+      iterate<BT, true>(S, c, sl, s, par);
+    } else {
+      if constexpr (std::is_same<BT, float>::value) replace_residual(S, c, s, par);   // BF16 solves run without it
+    }
+    // The compiler lays this branch out before the usual path and joins the
+    // two: loads it left in flight here would be waited for there.
+    __builtin_amdgcn_s_waitcnt(0);
+    __builtin_amdgcn_endpgm();
+  }
+  iterate<BT, false>(S, c, sl, s, par);
+}
+
+template <class BT>
+__global__ void __launch_bounds__(kFusedBlock, 2) k_fused(PcgSystem S, int par) {
+  fused_launch<BT>(S, xcd_block(blockIdx.x, S.fused_nwg), par);
+}
+
+template <class BT>
+__global__ void __launch_bounds__(kFusedBlock, 2)
+k_fused_batched(const PcgSystem* __restrict__ sys, const int* __restrict__ wg_sys, int par) {
+  const int b = xcd_block(blockIdx.x, gridDim.x);
+  const PcgSystem S = uniform_load(sys + uniform_load(wg_sys + b));
+  fused_launch<BT>(S, b - S.fused_wg0, par);
+}
+
+}  // namespace
+
+int pcg_fused_groups(int N) {
+  const int nslices = div_up(N, kSlice);
+  return nslices <= kFusedMaxSlices ? nslices : 0;
+}
+
+void launch_pcg_fused(const PcgSystem& S, bool bf16, int par, hipStream_t s, hipEvent_t t0, hipEvent_t t1) {
+  const dim3 grid(S.fused_nwg), block(kFusedBlock);
+  if (t0 && t1) {
+    if (bf16)
+      hipExtLaunchKernelGGL(k_fused<uint32_t>, grid, block, 0, s, t0, t1, 0, S, par);
+    else
+      hipExtLaunchKernelGGL(k_fused<float>, grid, block, 0, s, t0, t1, 0, S, par);
+  } else if (bf16) {
+    hipLaunchKernelGGL(k_fused<uint32_t>, grid, block, 0, s, S, par);
+  } else {
+    hipLaunchKernelGGL(k_fused<float>, grid, block, 0, s, S, par);
+  }
+}
+
+void launch_pcg_fused_batched(const PcgSystem* sys, const int* wg_sys, int nwg, int par, hipStream_t s) {
+  hipLaunchKernelGGL(k_fused_batched<float>, dim3(nwg), dim3(kFusedBlock), 0, s, sys, wg_sys, par);
+}
+
+}  // namespace bfal

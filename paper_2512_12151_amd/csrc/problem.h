@@ -57,6 +57,7 @@ struct bf_problem {
   long long cap_nnzb = 0, cap_cand = 0;
   long long nslot_u = 0, nslot_l = 0;   // slots of the sliced storage of the last step
   PcgScalars* host_sc = nullptr;
+  unsigned long long* host_stat = nullptr;   // pinned: a one-kernel solve's report (PcgSystem::hstat)
   // collision queries: the surface (built at the first call), two BVHs, the
   // colliding pairs and the active-set rebuild
   bool surf_ready = false;
@@ -145,6 +146,13 @@ inline PcgSystem system_of(bf_problem* pb) {
   S.spmv_nwg = pcg_spmv_groups(pb->N, pb->ctx->num_cu);
   S.vec_wg0 = 0;
   S.vec_nwg = pcg_vec_groups(pb->N);
+  S.fused_wg0 = 0;
+  // (its loads use 32-bit byte offsets: the upper blocks are its largest array)
+  const long long slots = pb->nslot_u + 2 * kSlice;
+  S.fused_nwg = 36 * slots < (1LL << 32) ? pcg_fused_groups(pb->N) : 0;
+  S.bhat = pb->bhat.as<float>();
+  S.aflags = pb->flags.as<int>();
+  S.hstat = nullptr;
   return S;
 }
 

@@ -83,6 +83,7 @@ struct bf_server {
   // batch thread only
   std::vector<int> active;
   DevBuf sys_dev, map_spmv, map_vec, status_dev;
+  int par = 0;   // parity of the next one-kernel launch
   PcgSystem* h_sys = nullptr;
   int* h_map = nullptr;
   int* h_status = nullptr;
@@ -198,16 +199,23 @@ void admission_loop(bf_server* sv, int worker) {
   }
 }
 
-// Rebuild and upload the batch table: every active system gets its SpMV and
-// update workgroups at consecutive offsets.
-bf_status upload_table(bf_server* sv, int* nwg_spmv, int* nwg_vec) {
+// Rebuild and upload the batch table: every active system gets its workgroups
+// at consecutive offsets, of the one-kernel iteration or of the SpMV and the
+// update.
+bf_status upload_table(bf_server* sv, int* nwg_spmv, int* nwg_vec, int* nwg_fused) {
   bf_context* c = sv->batch_ctx;
   const int n = (int)sv->active.size();
-  int ts = 0, tv = 0;
+  int ts = 0, tv = 0, tf = 0;
   for (int i : sv->active) {
-    ts += sv->slots[i].S.spmv_nwg;
-    tv += sv->slots[i].S.vec_nwg;
+    const PcgSystem& S = sv->slots[i].S;
+    if (S.fused_nwg) {
+      tf += S.fused_nwg;
+    } else {
+      ts += S.spmv_nwg;
+      tv += S.vec_nwg;
+    }
   }
+  const int total = ts + tv + tf;
   if (n > sv->h_sys_cap) {
     if (sv->h_sys) (void)hipHostFree(sv->h_sys);
     if (sv->h_status) (void)hipHostFree(sv->h_status);
@@ -217,33 +225,40 @@ bf_status upload_table(bf_server* sv, int* nwg_spmv, int* nwg_vec) {
     HIPCHK(c, hipHostMalloc((void**)&sv->h_status, sizeof(int) * kStatusInts * n, hipHostMallocDefault));
     sv->h_sys_cap = n;
   }
-  if (ts + tv > sv->h_map_cap) {
+  if (total > sv->h_map_cap) {
     if (sv->h_map) (void)hipHostFree(sv->h_map);
     sv->h_map = nullptr;
-    HIPCHK(c, hipHostMalloc((void**)&sv->h_map, sizeof(int) * (ts + tv), hipHostMallocDefault));
-    sv->h_map_cap = ts + tv;
+    HIPCHK(c, hipHostMalloc((void**)&sv->h_map, sizeof(int) * total, hipHostMallocDefault));
+    sv->h_map_cap = total;
   }
-  int os = 0, ov = 0;
+  int os = 0, ov = 0, of = 0;
   for (int k = 0; k < n; ++k) {
     PcgSystem S = sv->slots[sv->active[k]].S;
     S.spmv_wg0 = os;
     S.vec_wg0 = ov;
-    for (int b = 0; b < S.spmv_nwg; ++b) sv->h_map[os + b] = k;
-    for (int b = 0; b < S.vec_nwg; ++b) sv->h_map[ts + ov + b] = k;
-    os += S.spmv_nwg;
-    ov += S.vec_nwg;
+    S.fused_wg0 = of;
+    if (S.fused_nwg) {
+      for (int b = 0; b < S.fused_nwg; ++b) sv->h_map[ts + tv + of + b] = k;
+      of += S.fused_nwg;
+    } else {
+      for (int b = 0; b < S.spmv_nwg; ++b) sv->h_map[os + b] = k;
+      for (int b = 0; b < S.vec_nwg; ++b) sv->h_map[ts + ov + b] = k;
+      os += S.spmv_nwg;
+      ov += S.vec_nwg;
+    }
     sv->h_sys[k] = S;
   }
   // device tables grow geometrically (a reallocation frees the old buffer)
   const size_t want_sys = sizeof(PcgSystem) * std::max(n, 64);
-  const size_t want_map = sizeof(int) * std::max(ts + tv, 4096);
+  const size_t want_map = sizeof(int) * std::max(total, 4096);
   if (sv->sys_dev.bytes < sizeof(PcgSystem) * n) ALLOC(c, sv->sys_dev, 2 * want_sys);
-  if (sv->map_spmv.bytes < sizeof(int) * (ts + tv)) ALLOC(c, sv->map_spmv, 2 * want_map);
+  if (sv->map_spmv.bytes < sizeof(int) * total) ALLOC(c, sv->map_spmv, 2 * want_map);
   if (sv->status_dev.bytes < sizeof(int) * kStatusInts * n) ALLOC(c, sv->status_dev, 2 * kStatusInts * sizeof(int) * std::max(n, 64));
   HIPCHK(c, hipMemcpyAsync(sv->sys_dev.p, sv->h_sys, sizeof(PcgSystem) * n, hipMemcpyHostToDevice, c->stream));
-  HIPCHK(c, hipMemcpyAsync(sv->map_spmv.p, sv->h_map, sizeof(int) * (ts + tv), hipMemcpyHostToDevice, c->stream));
+  HIPCHK(c, hipMemcpyAsync(sv->map_spmv.p, sv->h_map, sizeof(int) * total, hipMemcpyHostToDevice, c->stream));
   *nwg_spmv = ts;
   *nwg_vec = tv;
+  *nwg_fused = tf;
   return BF_OK;
 }
 
@@ -303,7 +318,7 @@ void batch_loop(bf_server* sv) {
   (void)hipSetDevice(c->device);
   hipStream_t s = c->stream;
   bool changed = false;
-  int nwg_spmv = 0, nwg_vec = 0;
+  int nwg_spmv = 0, nwg_vec = 0, nwg_fused = 0;
   for (;;) {
     {
       std::unique_lock<std::mutex> lk(sv->mu);
@@ -316,7 +331,7 @@ void batch_loop(bf_server* sv) {
       }
     }
     if (changed) {
-      if (upload_table(sv, &nwg_spmv, &nwg_vec) != BF_OK) {
+      if (upload_table(sv, &nwg_spmv, &nwg_vec, &nwg_fused) != BF_OK) {
         // cannot run the batch: fail every active request
         for (int si : sv->active) {
           Request* r = sv->slots[si].req;
@@ -335,8 +350,11 @@ void batch_loop(bf_server* sv) {
     }
     const PcgSystem* sys = sv->sys_dev.as<PcgSystem>();
     const int* map = sv->map_spmv.as<int>();
-    for (int k = 0; k < sv->iters_per_round; ++k)
-      launch_pcg_iteration_batched(sys, map, nwg_spmv, map + nwg_spmv, nwg_vec, false, s);
+    for (int k = 0; k < sv->iters_per_round; ++k) {
+      if (nwg_fused) launch_pcg_fused_batched(sys, map + nwg_spmv + nwg_vec, nwg_fused, sv->par, s);
+      sv->par ^= 1;
+      if (nwg_spmv) launch_pcg_iteration_batched(sys, map, nwg_spmv, map + nwg_spmv, nwg_vec, false, s);
+    }
     const int n = (int)sv->active.size();
     hipLaunchKernelGGL(k_gather_status, dim3(div_up(n, kBlock)), dim3(kBlock), 0, s, sys, n,
                        sv->status_dev.as<int>());

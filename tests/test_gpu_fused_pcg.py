@@ -1,0 +1,93 @@
+"""The one-kernel PCG iteration (systems of up to 512 slices of 64 rows) at the
+edges of its range: slices that are not full, rows wider than one round of
+slots, the largest system it takes and the first one it leaves to the
+two-kernel iteration, iteration caps and sparse residual tests.
+
+The solution is checked against the assembled FP64 matrix and gradient that the
+step reports: the solver stops at |b - H32 p| <= tol |b| with H32 the matrix
+whose scaled blocks are rounded to FP32 (relative rounding 2^-24 per entry), so
+|b - H p| <= tol |b| + 2^-24 | |H| |p| | up to the rounding of the scaling
+itself, for which a factor of four is left on the second term."""
+import numpy as np
+import pytest
+import scipy.sparse as sp
+
+import scenes
+from paper_2512_12151_amd import bfal
+from scenes.configs import _finish
+from scenes.mesh import kuhn_box
+
+pytestmark = pytest.mark.gpu
+
+
+def _box(nx, ny, nz, seed=4):
+    """One box, its bottom fixed, jittered: no contacts."""
+    rest, tets = kuhn_box(nx, ny, nz, 0.1)
+    rng = np.random.default_rng(seed)
+    fixed = (rest[:, 2] == 0.0).astype(np.uint8)
+    xh = rest + rng.normal(0.0, 1e-3, rest.shape) * (1 - fixed)[:, None]
+    T = len(tets)
+    return _finish("box", seed, rest, tets, np.full(T, 1e5), np.full(T, 0.4), np.full(T, 1000.0), fixed, rest.copy(),
+                   xh, rest.copy(), 0.01, np.zeros((0, 4)), np.zeros((0, 4)), np.zeros(0), 1e4, 1e-3, 1e-5)
+
+
+def _crowded():
+    """Two stacked cubes with many pairs per vertex: rows of far more than 16 blocks."""
+    return scenes.tiny(n=5, n_pt=900, n_ee=900)
+
+
+CASES = [
+    ("63 rows", lambda: _box(2, 2, 6)),                  # 3 * 3 * 7: one slice, not full
+    ("64 rows", lambda: _box(3, 3, 3)),                  # exactly one slice
+    ("130 rows", lambda: _box(12, 4, 1)),                # 13 * 5 * 2: two slices and two rows
+    ("wide rows", _crowded),
+    ("512 slices", lambda: _box(31, 31, 31)),            # 32,768 rows: the largest
+    ("513 slices", lambda: _box(32, 31, 31)),            # 33,792 rows: two kernels
+]
+
+
+def _matrix(pb):
+    row_ptr, col, _, _, _ = pb.pattern()
+    blk = pb.blocks()
+    n = len(row_ptr) - 1
+    up = sp.bsr_matrix((blk, col, row_ptr), shape=(3 * n, 3 * n)).tocsr()
+    diag = sp.block_diag([blk[row_ptr[i]] for i in range(n)], format="csr") if n < 4000 else sp.bsr_matrix(
+        (blk[row_ptr[:-1]], np.arange(n), np.arange(n + 1)), shape=(3 * n, 3 * n)).tocsr()
+    return up + up.T - diag
+
+
+@pytest.mark.parametrize("name,make", CASES, ids=[c[0] for c in CASES])
+@pytest.mark.parametrize("check_every", [1, 5])
+def test_solution_of_the_assembled_system(name, make, check_every):
+    sc = make()
+    tol = 1e-5
+    ctx = bfal.Context(0)
+    pb = bfal.Problem.from_scene(ctx, sc)
+    p, st, status = pb.newton_step(tol=tol, check_every=check_every)
+    assert status == 0 and st["pcg_iters"] % check_every == 0
+    H, b = _matrix(pb), -pb.gradient().ravel()
+    r = np.linalg.norm(b - H @ p.ravel())
+    slack = 2.0 ** -24 * np.linalg.norm(abs(H) @ np.abs(p.ravel()))
+    print(name, check_every, "iterations", st["pcg_iters"], "residual", r / np.linalg.norm(b), flush=True)
+    # (the gradient comes back in FP32: 2^-24 of it on the right-hand side)
+    assert r <= tol * np.linalg.norm(b) + 4.0 * slack + 2.0 ** -24 * np.linalg.norm(b)
+    # the same again on the same problem: bit for bit
+    q, _, _ = pb.newton_step(tol=tol, check_every=check_every)
+    assert np.array_equal(p, q)
+
+
+@pytest.mark.parametrize("cap", [0, 1, 7, 40])
+def test_iteration_cap(cap):
+    pb = bfal.Problem.from_scene(bfal.Context(0), _crowded())
+    p, st, status = pb.newton_step(tol=1e-14, max_iter=cap)
+    assert status == bfal.BF_WARN_PCG_MAXITER and st["pcg_iters"] == cap
+    assert np.all(np.isfinite(p)) and (cap > 0) == bool(np.any(p != 0.0))
+
+
+def test_zero_right_hand_side():
+    sc = dict(_box(3, 3, 3))
+    sc["x_hat"] = sc["x"].copy()   # at rest: G = 0 up to the rounding of the stress
+    sc["x_tilde"] = sc["x"].copy()
+    pb = bfal.Problem.from_scene(bfal.Context(0), sc)
+    p, st, status = pb.newton_step(tol=1e-5)
+    assert status == 0 and np.all(np.isfinite(p)) and np.max(np.abs(p)) < 1e-12
