@@ -82,20 +82,22 @@ constexpr int kPRing = kXBatch + 1;
 
 // Partials of one PCG system: every workgroup writes one FP64 value per sum.
 constexpr int kMaxVecParts = 1024;    // workgroups of the update kernel per system
-constexpr int kMaxSpmvParts = 2048;   // workgroups of the SpMV per system
+constexpr int kMaxSpmvParts = 512;    // workgroups of the SpMV per system (one per compute unit at most)
 constexpr int kPartRR = 0;                              // r^T r, two slots (iterations k, k+1)
 constexpr int kPartRT = 2 * kMaxVecParts;               // |L r|^2
 constexpr int kPartPQ = 3 * kMaxVecParts;               // p^T H p
 constexpr int kPartRQ = kPartPQ + kMaxSpmvParts;        // r^T H p
 constexpr int kPartQQ = kPartRQ + kMaxSpmvParts;        // |H p|^2
-constexpr int kPartsPerSystem = 3 * kMaxVecParts + 3 * kMaxSpmvParts;
+constexpr int kPartsPerSystem = 6144;   // the two-kernel iteration's, or the one-kernel iteration's
+static_assert(kPartQQ + kMaxSpmvParts <= kPartsPerSystem, "they fit");
 
 constexpr int kSlice = 64;         // rows per slice of the sliced block storage (one wavefront)
 
 // One-kernel PCG (pcg_fused.hip): the largest system it takes, in slices (one
-// per workgroup).  Its partials are five doubles per slice, for two iterations.
+// per workgroup).  Its partials are five doubles per slice, for two iterations,
+// and two of a replaced residual.
 constexpr int kFusedMaxSlices = 512;
-static_assert(2 * kFusedMaxSlices * 5 <= kPartsPerSystem, "they fit the partials");
+static_assert((2 * 5 + 2) * kFusedMaxSlices <= kPartsPerSystem, "they fit the partials");
 
 // One symmetric block system of the PCG, H_hat = L^{-1} H L^{-T} with identity
 // diagonal blocks, in sliced storage (kSlice consecutive rows per slice, slot k

@@ -62,6 +62,8 @@
 // scalars (alpha, beta, convergence) are kept per system.
 #include <hip/hip_ext.h>
 
+#include <cstddef>
+
 #include "pcg_device.h"
 
 namespace bfal {
@@ -77,8 +79,7 @@ constexpr int kVecBlock = 256;                     // threads per update workgro
 template <int NT>
 __device__ inline double block_sum_all(double v) {
   __shared__ double red[NT / kWave];
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
+  v = wave_sum_all(v);
   __syncthreads();
   if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = v;
   __syncthreads();
@@ -92,12 +93,9 @@ __device__ inline double block_sum_all(double v) {
 template <int NT>
 __device__ inline void block_sum3(double& a, double& b, double& c) {
   __shared__ double red[3][NT / kWave];
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) {
-    a += __shfl_xor(a, off, kWave);
-    b += __shfl_xor(b, off, kWave);
-    c += __shfl_xor(c, off, kWave);
-  }
+  a = wave_sum_all(a);
+  b = wave_sum_all(b);
+  c = wave_sum_all(c);
   __syncthreads();
   if ((threadIdx.x & (kWave - 1)) == 0) {
     red[0][threadIdx.x / kWave] = a;
@@ -128,13 +126,13 @@ __device__ inline double block_max_all(double v) {
   return s;
 }
 
-// This thread's share of a partials array of n <= kMaxSpmvParts entries:
+// This thread's share of a partials array of n <= kMax entries:
 // a[t] + a[t + NT] + ... summed in that order, with every load issued before
 // the first add (the partials come from other XCDs through the Infinity
 // Cache; a dependent chain would wait one round trip per element).
-template <int NT>
+template <int NT, int kMax>
 __device__ __forceinline__ double thread_parts(const double* __restrict__ a, int n) {
-  constexpr int kPer = (kMaxSpmvParts + NT - 1) / NT;
+  constexpr int kPer = (kMax + NT - 1) / NT;
   double v[kPer];
 #pragma unroll
   for (int u = 0; u < kPer; ++u) {
@@ -154,13 +152,11 @@ template <int NT>
 __device__ inline void sum_parts3(const double* __restrict__ a, int na, const double* __restrict__ b, int nb,
                                   const double* __restrict__ c, int nc, double& sa, double& sb, double& sc) {
   __shared__ double red[3][NT / kWave];
-  double va = thread_parts<NT>(a, na), vb = thread_parts<NT>(b, nb), vc = thread_parts<NT>(c, nc);
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) {
-    va += __shfl_xor(va, off, kWave);
-    vb += __shfl_xor(vb, off, kWave);
-    vc += __shfl_xor(vc, off, kWave);
-  }
+  double va = thread_parts<NT, kMaxVecParts>(a, na), vb = thread_parts<NT, kMaxVecParts>(b, nb),
+         vc = thread_parts<NT, kMaxVecParts>(c, nc);
+  va = wave_sum_all(va);
+  vb = wave_sum_all(vb);
+  vc = wave_sum_all(vc);
   __syncthreads();
   if ((threadIdx.x & (kWave - 1)) == 0) {
     red[0][threadIdx.x / kWave] = va;
@@ -177,32 +173,52 @@ __device__ inline void sum_parts3(const double* __restrict__ a, int na, const do
   }
 }
 
-// Four fixed-order sums in one pass (as sum_parts3).
-template <int NT>
-__device__ inline void sum_parts4(const double* __restrict__ a, int na, const double* __restrict__ b, int nb,
-                                  const double* __restrict__ c, int nc, const double* __restrict__ d, int nd,
-                                  double& sa, double& sb, double& sc, double& sd) {
-  __shared__ double red[4][NT / kWave];
-  double v[4] = {thread_parts<NT>(a, na), thread_parts<NT>(b, nb), thread_parts<NT>(c, nc), thread_parts<NT>(d, nd)};
+// The update's four sums: r^T r over its own workgroups' partials, p^T q,
+// r^T q and q^T q over the SpMV's.  load() asks for them (unconditionally:
+// past a count the last entry is read again and not added), sum() adds them in
+// a fixed order.  Asked for before the vectors' operands, they are waited for
+// without waiting for those.
+struct UpdateSums {
+  static constexpr int kPerV = kMaxVecParts / kVecBlock, kPerS = kMaxSpmvParts / kVecBlock;
+  static_assert(kMaxVecParts % kVecBlock == 0 && kMaxSpmvParts % kVecBlock == 0, "whole rounds");
+  double r[kPerV], q[3][kPerS];
+
+  __device__ __forceinline__ void load(const double* __restrict__ part, int k, int nv, int ns) {
+    const int t = threadIdx.x;
+    const double* __restrict__ a = part + kPartRR + (k & 1) * kMaxVecParts;
 #pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1)
+    for (int u = 0; u < kPerV; ++u) r[u] = a[min(t + u * kVecBlock, nv - 1)];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) v[m] += __shfl_xor(v[m], off, kWave);
-  __syncthreads();
-  if ((threadIdx.x & (kWave - 1)) == 0)
+    for (int m = 0; m < 3; ++m)
 #pragma unroll
-    for (int m = 0; m < 4; ++m) red[m][threadIdx.x / kWave] = v[m];
-  __syncthreads();
-  double t[4] = {0.0, 0.0, 0.0, 0.0};
+      for (int u = 0; u < kPerS; ++u) q[m][u] = part[kPartPQ + m * kMaxSpmvParts + min(t + u * kVecBlock, ns - 1)];
+  }
+
+  __device__ __forceinline__ void sum(int nv, int ns, double out[4]) const {
+    static_assert(kPartRQ == kPartPQ + kMaxSpmvParts && kPartQQ == kPartRQ + kMaxSpmvParts, "three in a row");
+    __shared__ double red[4][kVecBlock / kWave];
+    const int t = threadIdx.x;
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int w = 0; w < NT / kWave; ++w)
+    for (int u = 0; u < kPerV; ++u) v[0] += t + u * kVecBlock < nv ? r[u] : 0.0;
 #pragma unroll
-    for (int m = 0; m < 4; ++m) t[m] += red[m][w];
-  sa = t[0];
-  sb = t[1];
-  sc = t[2];
-  sd = t[3];
-}
+    for (int m = 0; m < 3; ++m)
+#pragma unroll
+      for (int u = 0; u < kPerS; ++u) v[1 + m] += t + u * kVecBlock < ns ? q[m][u] : 0.0;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) v[m] = wave_sum_all(v[m]);
+    if ((t & (kWave - 1)) == 0)
+#pragma unroll
+      for (int m = 0; m < 4; ++m) red[m][t / kWave] = v[m];
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      out[m] = 0.0;
+#pragma unroll
+      for (int w = 0; w < kVecBlock / kWave; ++w) out[m] += red[m][w];
+    }
+  }
+};
 
 // Fixed-order sum of part[0..n) by the whole workgroup (same value in every workgroup).
 template <int NT>
@@ -297,13 +313,14 @@ struct SliceCursor {
 // replacement is due) and the workgroup must return.  Called by the whole
 // workgroup.
 __device__ inline bool spmv_begin(const PcgSystem& S, int lb, bool leader, int& k, SliceCursor& c) {
-  const int wave = threadIdx.x / kSlice, lane = threadIdx.x % kSlice;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kSlice), lane = threadIdx.x % kSlice;
   PcgScalars* sc = S.sc;
-  const int every = sc->check_every, brk = sc->brk;
-  k = sc->iter;
+  // (words that this kernel does not write, and the plan, come through the scalar cache)
+  const int every = uniform_load(&sc->check_every), brk = uniform_load(&sc->brk);
+  k = uniform_load(&sc->iter);
   const int part = lb * kSlicesPerGroup + wave;
-  c.j0 = S.wave_ptr[part];
-  c.j1 = S.wave_ptr[part + 1];
+  c.j0 = uniform_load(S.wave_ptr + part);
+  c.j1 = uniform_load(S.wave_ptr + part + 1);
   // r^T r and |L r|^2 partials (the latter used on check iterations only);
   // every load is issued (indices past the count re-read the last entry and
   // are not added), so later waits count the loads in order
@@ -322,11 +339,17 @@ __device__ inline bool spmv_begin(const PcgSystem& S, int lb, bool leader, int& 
   }
   // an empty range reads slice 0 and is not walked
   const int jf = c.j0 < c.j1 ? c.j0 : 0, jl = c.j0 < c.j1 ? c.j1 - 1 : 0;
-  c.sl = S.wave_slices[jf];
-  c.sl1 = S.wave_slices[min(jf + 1, jl)];
-  c.sl2 = S.wave_slices[min(jf + 2, jl)];
-  c.bu = S.sbu[c.sl]; c.eu = S.sbu[c.sl + 1]; c.bl = S.sbl[c.sl]; c.el = S.sbl[c.sl + 1];
-  c.nbu = S.sbu[c.sl1]; c.neu = S.sbu[c.sl1 + 1]; c.nbl = S.sbl[c.sl1]; c.nel = S.sbl[c.sl1 + 1];
+  c.sl = uniform_load(S.wave_slices + jf);
+  c.sl1 = uniform_load(S.wave_slices + min(jf + 1, jl));
+  c.sl2 = uniform_load(S.wave_slices + min(jf + 2, jl));
+  c.bu = uniform_load(S.sbu + c.sl);
+  c.eu = uniform_load(S.sbu + c.sl + 1);
+  c.bl = uniform_load(S.sbl + c.sl);
+  c.el = uniform_load(S.sbl + c.sl + 1);
+  c.nbu = uniform_load(S.sbu + c.sl1);
+  c.neu = uniform_load(S.sbu + c.sl1 + 1);
+  c.nbl = uniform_load(S.sbl + c.sl1);
+  c.nel = uniform_load(S.sbl + c.sl1 + 1);
   load_step_indices(S.scol, S.sent, c.bu + lane, c.bl + lane, c.uc, c.lb, c.lc);
   const bool first = (int)threadIdx.x < nv;
   double a = first ? va[0] : 0.0, b = first ? vb[0] : 0.0;
@@ -376,8 +399,9 @@ __device__ inline void spmv_slices(const PcgSystem& S, int k, SliceCursor& c, do
   const BT* __restrict__ blk = static_cast<const BT*>(S.blk);
   const int jl = c.j1 - 1;
   for (int j = c.j0; j < c.j1; ++j) {
-    const int sl3 = S.wave_slices[min(j + 3, jl)];
-    const int b2u = S.sbu[c.sl2], e2u = S.sbu[c.sl2 + 1], b2l = S.sbl[c.sl2], e2l = S.sbl[c.sl2 + 1];
+    const int sl3 = uniform_load(S.wave_slices + min(j + 3, jl));
+    const int b2u = uniform_load(S.sbu + c.sl2), e2u = uniform_load(S.sbu + c.sl2 + 1);
+    const int b2l = uniform_load(S.sbl + c.sl2), e2l = uniform_load(S.sbl + c.sl2 + 1);
     const int row = c.sl * kSlice + lane;
     const bool live = row < S.N;
     // read unconditionally (a pad row reads row N - 1 and is not used), so no
@@ -460,45 +484,42 @@ __device__ __forceinline__ const float* dir_of(const PcgSystem& S, int j) { retu
 __device__ __forceinline__ void load_update_operands(const PcgSystem& S, int k, bool flush, int j0, long long ch,
                                                      bool check, UpdateOperands& o) {
   const int t = threadIdx.x;
-  const long long n4 = S.N4, nf4 = 3 * n4 / 4;
+  // (indices past the end read the last entry again and are not used: no
+  // branch between the loads)
+  const long long n4 = S.N4, last = 3 * n4 / 4 - 1;
   const float4* __restrict__ p4 = reinterpret_cast<const float4*>(dir_of(S, k));
   const float4* __restrict__ q4 = reinterpret_cast<const float4*>(S.q);
   const double2* __restrict__ x2 = reinterpret_cast<const double2*>(S.x);
   const float4* __restrict__ r4 = reinterpret_cast<const float4*>(S.r);
   const float4* __restrict__ l4 = reinterpret_cast<const float4*>(S.Lf);
+  long long f[3];
+#pragma unroll
+  for (int m = 0; m < 3; ++m) f[m] = min(ch * 3 * kVecBlock + m * kVecBlock + t, last);
 #pragma unroll
   for (int m = 0; m < 3; ++m) {
-    const long long f = ch * 3 * kVecBlock + m * kVecBlock + t;
-    if (f < nf4) {
-      o.p[m] = p4[f];
-      o.q[m] = q4[f];
-      o.r[m] = r4[f];
-    }
+    o.p[m] = p4[f[m]];
+    o.q[m] = q4[f[m]];
+    o.r[m] = r4[f[m]];
   }
   if (flush) {
 #pragma unroll
     for (int m = 0; m < 3; ++m) {
-      const long long f = ch * 3 * kVecBlock + m * kVecBlock + t;
-      if (f < nf4) {
-        o.xa[m] = x2[2 * f];
-        o.xb[m] = x2[2 * f + 1];
-      }
+      o.xa[m] = x2[2 * f[m]];
+      o.xb[m] = x2[2 * f[m] + 1];
     }
 #pragma unroll
     for (int u = 0; u < kXBatch - 1; ++u) {
       const int j = j0 + u < k ? j0 + u : k;
       const float4* __restrict__ pj4 = reinterpret_cast<const float4*>(dir_of(S, j));
 #pragma unroll
-      for (int m = 0; m < 3; ++m) {
-        const long long f = ch * 3 * kVecBlock + m * kVecBlock + t;
-        if (f < nf4) o.pj[u][m] = pj4[f];
-      }
+      for (int m = 0; m < 3; ++m) o.pj[u][m] = pj4[f[m]];
     }
   }
-  const long long v0 = ch * 4 * kVecBlock + 4LL * t;
-  if (check && v0 < n4)
+  if (check) {
+    const long long v0 = min(ch * 4 * kVecBlock + 4LL * t, n4 - 4);
 #pragma unroll
     for (int m = 0; m < 6; ++m) o.l[m] = l4[(m * n4 + v0) / 4];
+  }
 }
 
 // x += alpha_j p_j for j0 <= j <= k, in order (flush iterations only).
@@ -580,9 +601,12 @@ __device__ __forceinline__ void update_chunk(const PcgSystem& S, float4* __restr
 // reduction (a workgroup usually owns one chunk).
 __device__ inline void update_nodes(const PcgSystem& S, int lb) {
   PcgScalars* sc = S.sc;
-  // the control words are read together (k, every and xbase are also used
-  // after the test of `done`, so their loads stay with it)
-  const int done = sc->done, k = sc->ks, every = sc->check_every, xbase = sc->xbase;
+  // the control words, through the scalar cache in one load (this kernel writes none of them)
+  static_assert(offsetof(PcgScalars, ks) == 0 && offsetof(PcgScalars, done) == 4 &&
+                    offsetof(PcgScalars, check_every) == 8 && offsetof(PcgScalars, xbase) == 12, "one load");
+  const int4 cw = uniform_load(reinterpret_cast<const int4*>(sc));
+  const int k = cw.x, done = cw.y, every = cw.z, xbase = cw.w;
+  if (done) return;
   const bool check = ((k + 1) % every) == 0;
   double* part = S.part;
   __shared__ float4 rs[3 * kVecBlock];
@@ -592,13 +616,14 @@ __device__ inline void update_nodes(const PcgSystem& S, int lb) {
   // x takes alpha_j p_j, j0 <= j <= k, on every kXBatch-th iteration
   const bool flush = ((k + 1) % kXBatch) == 0;
   const int j0 = max(xbase, k + 1 - kXBatch);
-  UpdateOperands o;
-  if (!done && lb < nchunk) load_update_operands(S, k, flush, j0, lb, check, o);
-  if (done) return;
   const float ah = sc->alpha_hist[threadIdx.x % kXBatch];
-  double rho, pq, rq, qq;
-  sum_parts4<kVecBlock>(part + kPartRR + (k & 1) * kMaxVecParts, S.vec_nwg, part + kPartPQ, S.spmv_nwg,
-                        part + kPartRQ, S.spmv_nwg, part + kPartQQ, S.spmv_nwg, rho, pq, rq, qq);
+  UpdateSums us;
+  us.load(part, k, S.vec_nwg, S.spmv_nwg);
+  UpdateOperands o;
+  load_update_operands(S, k, flush, j0, lb, check, o);
+  double sums[4];
+  us.sum(S.vec_nwg, S.spmv_nwg, sums);
+  const double rho = sums[0], pq = sums[1], rq = sums[2], qq = sums[3];
   const bool leader = lb == 0 && threadIdx.x == 0;
   if (!(pq > 0.0)) {
     if (leader) {

@@ -1,10 +1,25 @@
 // Device helpers shared by the PCG kernels (pcg.hip, pcg_fused.hip).
 #pragma once
 
+#include <type_traits>
+
 #include "common.h"
 #include "wave_ops.h"
 
 namespace bfal {
+
+// A value that no workgroup of the launch writes, loaded through the scalar cache.
+template <class T>
+__device__ __forceinline__ T uniform_load(const T* p) {
+  static_assert(sizeof(T) % 4 == 0 && std::is_trivially_copyable<T>::value, "whole words");
+  const auto* w = (const __attribute__((address_space(4))) uint32_t*)(p);
+  uint32_t u[sizeof(T) / 4];
+#pragma unroll
+  for (unsigned m = 0; m < sizeof(T) / 4; ++m) u[m] = w[m];
+  T v;
+  __builtin_memcpy(&v, u, sizeof(T));
+  return v;
+}
 
 // Dispatch ids go round-robin over the 8 XCDs: give each XCD one contiguous
 // range of logical workgroups.

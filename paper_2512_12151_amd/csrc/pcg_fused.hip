@@ -89,22 +89,15 @@ __device__ __forceinline__ void load_block32(const uint32_t* __restrict__ base, 
   b[8] = __uint_as_float(w.v[4] << 16);
 }
 
-// A value that no workgroup of the launch writes, loaded through the scalar cache.
-template <class T>
-__device__ __forceinline__ T uniform_load(const T* p) {
-  static_assert(sizeof(T) % 4 == 0 && std::is_trivially_copyable<T>::value, "whole words");
-  const auto* w = (const __attribute__((address_space(4))) uint32_t*)(p);
-  uint32_t u[sizeof(T) / 4];
-#pragma unroll
-  for (unsigned m = 0; m < sizeof(T) / 4; ++m) u[m] = w[m];
-  T v;
-  __builtin_memcpy(&v, u, sizeof(T));
-  return v;
-}
-
-// Partial sum m (r^T r, |L r|^2, p^T q, r^T q, q^T q) of state k, one per workgroup.
+// Partial sum m (r^T r, |L r|^2, p^T q, r^T q, q^T q) of state k, one per
+// workgroup; and r^T r and |L r|^2 of a replaced residual, in a place of their
+// own: the launch that reads them (kFresh) writes the sums of the same k, and
+// its workgroups do not run in step.
 __device__ __forceinline__ double* record(const PcgSystem& S, int k, int m) {
   return S.part + ((k & 1) * 5 + m) * kFusedMaxSlices;
+}
+__device__ __forceinline__ double* replaced_record(const PcgSystem& S, int m) {
+  return S.part + (10 + m) * kFusedMaxSlices;
 }
 
 // The launch's report to the host (pinned memory): launches made and, once
@@ -154,8 +147,8 @@ __device__ __forceinline__ void replace_residual(const PcgSystem& S, PcgCtl c, i
   rr = wave_sum_all(rr);
   rt = wave_sum_all(rt);
   if (t == 0) {
-    record(S, c.k, 0)[sl] = rr;
-    record(S, c.k, 1)[sl] = rt;
+    replaced_record(S, 0)[sl] = rr;
+    replaced_record(S, 1)[sl] = rt;
     if (sl == 0) {
       c.mode = kFresh;
       hand_on(S, c, par);
@@ -201,8 +194,9 @@ __device__ __forceinline__ void iterate(const PcgSystem& S, const PcgCtl& c, Sli
   const int nrec = S.fused_nwg;
   double rec[kRecPerLane], rec1[kRecPerLane];
   {
-    const double* __restrict__ a = record(S, k, wv == 0 ? 0 : wv + 1);
-    const double* __restrict__ b = wv == 0 ? record(S, k, 1) : a;   // (unconditional: see Slice)
+    const double* __restrict__ a = kFreshState ? replaced_record(S, 0) : record(S, k, wv == 0 ? 0 : wv + 1);
+    // (unconditional: see Slice)
+    const double* __restrict__ b = kFreshState ? replaced_record(S, 1) : wv == 0 ? record(S, k, 1) : a;
 #pragma unroll
     for (int u = 0; u < kRecPerLane; ++u) rec[u] = a[min(lane + u * kWave, nrec - 1)];
 #pragma unroll

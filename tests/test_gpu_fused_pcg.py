@@ -91,3 +91,29 @@ def test_zero_right_hand_side():
     pb = bfal.Problem.from_scene(bfal.Context(0), sc)
     p, st, status = pb.newton_step(tol=1e-5)
     assert status == 0 and np.all(np.isfinite(p)) and np.max(np.abs(p)) < 1e-12
+
+
+def test_batched_solves_equal_the_same_solves_alone():
+    """Many requests in one batch: their workgroups do not run in step, so every
+    launch of a solve meets workgroups that start after others have ended.
+    Residual replacements included (several hundred iterations each)."""
+    reqs = [scenes.serve_request(i) for i in range(40)]
+    reqs = [r for r in reqs if len(r["x"]) <= 16000][:20]
+    ctx = bfal.Context(0)
+    alone = []
+    for r in reqs:
+        pb = bfal.Problem.from_scene(ctx, r)
+        alone.append(pb.newton_step(tol=1e-7)[0])
+        pb.close()
+    srv = bfal.Server(0, max_active=64)
+    for rep in range(6):
+        left = {}
+        for i, r in enumerate(reqs):
+            srv.submit(100 * rep + i, r, tol=1e-7)
+            left[100 * rep + i] = i
+        while left:
+            for q in srv.poll():
+                p, _, _, status = srv.result(q)
+                i = left.pop(q)
+                assert status == 0 and np.array_equal(p, alone[i]), f"round {rep}, request {i} ({len(p)} nodes)"
+    srv.close()
