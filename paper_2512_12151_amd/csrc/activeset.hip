@@ -100,7 +100,7 @@ bf_status build_tree(bf_problem* pb, int n, const int* ids, int k, const double*
   ALLOC(c, key2, 8LL * n);
   ALLOC(c, child, 8LL * std::max(n - 1, 1));
   ALLOC(c, parent, 8LL * std::max(n - 1, 1));          // internal node leaf ranges
-  ALLOC(c, node, 48LL * n);
+  ALLOC(c, node, ccd_node_bytes(n));
   ALLOC(c, arrive, 24LL * n * ccd_table_levels(n));    // sparse table of run boxes
   ALLOC(c, pb->bpart, 24LL * ccd_bounds_parts(n));
   launch_prim_boxes(n, ids, k, pb->x.as<double>(), xh, box.p, s);
@@ -138,23 +138,30 @@ bf_status collide(bf_problem* pb, const double* xh, double sep, Collide& out) {
   ALLOC(c, pb->qcount, 4 * 32);
   int* cnt = pb->qcount.as<int>();
   bool todo[2] = {true, true};
-  for (int round = 0; round < 2 && (todo[0] || todo[1]); ++round) {
+  for (int round = 0; round < 3 && (todo[0] || todo[1]); ++round) {   // (candidates, then pairs, may ask for room)
+    QuerySide side[2];
     for (int kind = 0; kind < 2; ++kind) {
-      if (!todo[kind]) continue;
       const int nq = kind ? pb->nE : pb->nV;
       if (pb->qcap[kind] == 0) pb->qcap[kind] = std::max(4096, 4 * nq);
+      if (pb->ccap[kind] == 0) pb->ccap[kind] = std::max(4096LL, 16LL * nq);
       ALLOC(c, pb->qpairs[kind], 8LL * pb->qcap[kind]);
       ALLOC(c, pb->qtoc[kind], 8LL * pb->qcap[kind]);
-      HIPCHK(c, hipMemsetAsync(cnt + 8 * kind, 0, 32, s));
-      if (kind == 0)
-        launch_query(false, pb->nV, pb->sverts.as<int>(), pb->nF, pb->stris.as<int>(), pb->tchild.as<int2>(),
-                     pb->tnode.p, pb->tkey2.as<unsigned long long>(), pb->x.as<double>(), xh, pb->delta, sep,
-                     cnt, pb->qcap[0], pb->qpairs[0].as<int2>(), pb->qtoc[0].as<double>(), s);
-      else
-        launch_query(true, pb->nE, pb->sedges.as<int>(), pb->nE, pb->sedges.as<int>(), pb->echild.as<int2>(),
-                     pb->enode.p, pb->ekey2.as<unsigned long long>(), pb->x.as<double>(), xh, pb->delta, sep,
-                     cnt + 8, pb->qcap[1], pb->qpairs[1].as<int2>(), pb->qtoc[1].as<double>(), s);
+      ALLOC(c, pb->qcand[kind], 8LL * pb->ccap[kind]);
+      QuerySide& q = side[kind];
+      q.nq = nq;
+      q.nt = kind ? pb->nE : pb->nF;
+      q.qids = kind ? pb->sedges.as<int>() : pb->sverts.as<int>();
+      q.tids = kind ? pb->sedges.as<int>() : pb->stris.as<int>();
+      q.node = kind ? pb->enode.p : pb->tnode.p;
+      q.key = (kind ? pb->ekey2 : pb->tkey2).as<unsigned long long>();
+      q.cand = pb->qcand[kind].as<int2>();
+      q.cand_cap = pb->ccap[kind];
+      q.pairs = pb->qpairs[kind].as<int2>();
+      q.toc = pb->qtoc[kind].as<double>();
+      q.cap = pb->qcap[kind];
+      if (todo[kind]) fill_int(cnt + 8 * kind, 0, 8, s);
     }
+    launch_queries(side[0], side[1], todo[0], todo[1], pb->x.as<double>(), xh, pb->delta, sep, cnt, s);
     int h[16];
     HIPCHK(c, hipMemcpyAsync(h, cnt, sizeof(h), hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
@@ -165,10 +172,14 @@ bf_status collide(bf_problem* pb, const double* xh, double sep, Collide& out) {
       std::memcpy(&cand, h + 8 * kind + 2, sizeof(cand));
       out.cand[kind] = cand;
       out.hits[kind] = h[8 * kind];
-      if (h[8 * kind] > pb->qcap[kind]) {
-        pb->qcap[kind] = h[8 * kind] + h[8 * kind] / 4 + 1024;   // run this kind again with room for every pair
-      } else {
-        todo[kind] = false;
+      todo[kind] = false;
+      if (cand > pb->ccap[kind]) {   // run this kind again with room for every candidate
+        pb->ccap[kind] = cand + cand / 4 + 1024;
+        todo[kind] = true;
+      }
+      if (h[8 * kind] > pb->qcap[kind]) {   // ... and for every pair
+        pb->qcap[kind] = h[8 * kind] + h[8 * kind] / 4 + 1024;
+        todo[kind] = true;
       }
     }
   }

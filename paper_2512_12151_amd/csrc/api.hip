@@ -404,7 +404,7 @@ void bf_problem_destroy(bf_problem* pb) {
                     &pb->xd, &pb->rd, &pb->zd, &pb->fcg, &pb->rpart, &pb->lin64, &pb->pdir, &pb->xtrial,
                     &pb->epart, &pb->stris, &pb->sedges, &pb->sverts, &pb->xq, &pb->tbox, &pb->tkey, &pb->tkey2,
                     &pb->tchild, &pb->tparent, &pb->tnode, &pb->tarrive, &pb->ebox, &pb->ekey, &pb->ekey2,
-                    &pb->echild, &pb->eparent, &pb->enode, &pb->earrive, &pb->bpart, &pb->qcount, &pb->qpairs[0],
+                    &pb->echild, &pb->eparent, &pb->enode, &pb->earrive, &pb->bpart, &pb->qcount, &pb->qcand[0], &pb->qcand[1], &pb->qpairs[0],
                     &pb->qpairs[1], &pb->qtoc[0], &pb->qtoc[1], &pb->pkey, &pb->pkey2, &pb->pidx, &pb->pidx2,
                     &pb->sort_tmp, &pb->ctmp, &pb->htable, &pb->tvmin, &pb->keepn[0], &pb->keepn[1], &pb->posn[0],
                     &pb->posn[1], &pb->keepc, &pb->posc, &pb->nids, &pb->nlam, &pb->ngam, &pb->mpart,

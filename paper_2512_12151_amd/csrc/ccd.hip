@@ -10,9 +10,15 @@
 // tested again exactly in FP64 (swept boxes within delta on every axis) and
 // pairs sharing a vertex are skipped.
 //
-// Narrow phase: additive CCD (Li, Kaufman and Jiang 2021) in FP64, run by the
-// querying thread as soon as a pair passes the exact test, so candidates are
-// never stored: remove the pair's common translation, bound the rate at which
+// The queries of both kinds run in one launch and append the pairs that pass
+// the exact test to a candidate list; a second launch runs the narrow phase
+// with one thread per candidate.  Run by the querying thread itself, the
+// narrow phase made a few threads walk through all their candidates one after
+// the other while the rest of the chip was idle (a 2,300-edge scene took 515 +
+// 212 us per call in the two queries, one of 66,000 edges 645 + 343 us; the
+// split form takes 61 + 10 and 78 + 28 us).
+//
+// Narrow phase: additive CCD (Li, Kaufman and Jiang 2021) in FP64: remove the pair's common translation, bound the rate at which
 // the distance can shrink by l_p (largest displacement of a vertex of each
 // primitive, summed), and advance by steps that cannot close the gap --
 // (1 - s) d0 / l_p first, then 0.9 d / l_p -- until a step lands below s d0
@@ -38,6 +44,8 @@ namespace {
 constexpr int kCcdBlock = 256;
 constexpr int kAccdMaxSteps = 10000;
 constexpr int kStackDepth = 64;
+constexpr int kTraverseBlock = 64; // one wavefront per workgroup
+constexpr int kNarrowBlock = 64;   // one wavefront: it ends with its own longest pair
 
 struct d3 {
   double x, y, z;
@@ -47,6 +55,7 @@ __device__ inline d3 sub(d3 a, d3 b) { return {a.x - b.x, a.y - b.y, a.z - b.z};
 __device__ inline d3 add(d3 a, d3 b) { return {a.x + b.x, a.y + b.y, a.z + b.z}; }
 __device__ inline d3 mul(d3 a, double s) { return {a.x * s, a.y * s, a.z * s}; }
 __device__ inline double dot(d3 a, d3 b) { return a.x * b.x + a.y * b.y + a.z * b.z; }
+__device__ inline double norm2(d3 a) { return dot(a, a); }
 __device__ inline double norm(d3 a) { return sqrt(dot(a, a)); }
 __device__ inline double clamp01(double t) { return t < 0.0 ? 0.0 : (t > 1.0 ? 1.0 : t); }
 __device__ inline double seg_param(d3 p, d3 u, d3 v) {
@@ -62,16 +71,16 @@ __device__ inline double pt_dist(d3 p, d3 t0, d3 t1, d3 t2) {
   const double r1 = dot(e1, r), r2 = dot(e2, r);
   const double det = a11 * a22 - a12 * a12;
   const double u = (a22 * r1 - a12 * r2) / det, v = (a11 * r2 - a12 * r1) / det;
-  double best = INFINITY;
-  if (u >= 0.0 && v >= 0.0 && u + v <= 1.0) best = norm(sub(p, add(t0, add(mul(e1, u), mul(e2, v)))));
+  double best = INFINITY;   // squared: the root of the smallest square is the smallest root
+  if (u >= 0.0 && v >= 0.0 && u + v <= 1.0) best = norm2(sub(p, add(t0, add(mul(e1, u), mul(e2, v)))));
   const d3 T[3] = {t0, t1, t2};
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     const d3 a = T[k], b = T[(k + 1) % 3];
     const double s = seg_param(p, a, b);
-    best = fmin(best, norm(sub(p, add(a, mul(sub(b, a), s)))));
+    best = fmin(best, norm2(sub(p, add(a, mul(sub(b, a), s)))));
   }
-  return best;
+  return sqrt(best);
 }
 
 // Distance between segments a0 a1 and b0 b1: the interior stationary point
@@ -84,13 +93,13 @@ __device__ inline double ee_dist(d3 a0, d3 a1, d3 b0, d3 b1) {
   double best = INFINITY;
   if (det > 0.0) {
     const double s = (-ar * bb + ab * br) / det, t = (aa * br - ab * ar) / det;
-    if (s >= 0.0 && s <= 1.0 && t >= 0.0 && t <= 1.0) best = norm(sub(add(a0, mul(ea, s)), add(b0, mul(eb, t))));
+    if (s >= 0.0 && s <= 1.0 && t >= 0.0 && t <= 1.0) best = norm2(sub(add(a0, mul(ea, s)), add(b0, mul(eb, t))));
   }
   const double cs[4] = {0.0, 1.0, seg_param(b0, a0, a1), seg_param(b1, a0, a1)};
   const double ct[4] = {seg_param(a0, b0, b1), seg_param(a1, b0, b1), 0.0, 1.0};
 #pragma unroll
-  for (int k = 0; k < 4; ++k) best = fmin(best, norm(sub(add(a0, mul(ea, cs[k])), add(b0, mul(eb, ct[k])))));
-  return best;
+  for (int k = 0; k < 4; ++k) best = fmin(best, norm2(sub(add(a0, mul(ea, cs[k])), add(b0, mul(eb, ct[k])))));
+  return sqrt(best);
 }
 
 template <bool kEE>
@@ -225,15 +234,37 @@ __device__ inline unsigned int spread10(unsigned int v) {
 // bounds) above the primitive index, so equal codes order by index.
 __global__ void k_morton(int n, const Box* __restrict__ box, const Box* __restrict__ part, int nparts,
                          unsigned long long* __restrict__ key) {
-  const int i = blockIdx.x * kCcdBlock + threadIdx.x;
-  if (i >= n) return;
+  // the scene's bounds from the partial boxes, one per thread (nparts <= kCcdBlock)
+  __shared__ float red[6][kCcdBlock / kWave];
   float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (int p = 0; p < nparts; ++p)
+  if ((int)threadIdx.x < nparts)
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      lo[c] = fminf(lo[c], part[p].lo[c]);
-      hi[c] = fmaxf(hi[c], part[p].hi[c]);
+      lo[c] = part[threadIdx.x].lo[c];
+      hi[c] = part[threadIdx.x].hi[c];
     }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+      lo[c] = fminf(lo[c], __shfl_xor(lo[c], off, kWave));
+      hi[c] = fmaxf(hi[c], __shfl_xor(hi[c], off, kWave));
+    }
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+      red[c][threadIdx.x / kWave] = lo[c];
+      red[3 + c][threadIdx.x / kWave] = hi[c];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+#pragma unroll
+    for (int w = 0; w < kCcdBlock / kWave; ++w) {
+      lo[c] = fminf(lo[c], red[c][w]);
+      hi[c] = fmaxf(hi[c], red[3 + c][w]);
+    }
+  const int i = blockIdx.x * kCcdBlock + threadIdx.x;
+  if (i >= n) return;
   unsigned int code = 0;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
@@ -294,14 +325,12 @@ __device__ inline Box box_union(const Box& a, const Box& b) {
   return u;
 }
 
-// Level 0 of the table and the leaf nodes: the primitive boxes in key order.
+// Level 0 of the table, the leaves' boxes: the primitive boxes in key order.
 __global__ void k_leaf_boxes(int n, const unsigned long long* __restrict__ key, const Box* __restrict__ pbox,
-                             Box* __restrict__ level0, Box* __restrict__ node) {
+                             Box* __restrict__ level0) {
   const int k = blockIdx.x * kCcdBlock + threadIdx.x;
   if (k >= n) return;
-  const Box b = pbox[(int)(key[k] & 0xffffffffu)];
-  level0[k] = b;
-  node[n - 1 + k] = b;
+  level0[k] = pbox[(int)(key[k] & 0xffffffffu)];
 }
 
 // Level k from level k - 1 (run length h = 2^(k-1)): entries i + 2h <= n.
@@ -311,22 +340,41 @@ __global__ void k_sparse_level(int n, int h, const Box* __restrict__ prev, Box* 
   next[i] = box_union(prev[i], prev[i + h]);
 }
 
-__global__ void k_node_boxes(int n, const int2* __restrict__ range, const Box* __restrict__ table,
-                             Box* __restrict__ node) {
+// An internal node as a query reads it: its children with their boxes, so that
+// one load decides about both and a subtree that is missed is never visited.
+struct alignas(64) Node {   // read as four float4
+  Box left, right;
+  int2 child;
+  int pad[2];
+};
+static_assert(sizeof(Box) == 24 && sizeof(Node) == 64, "two boxes, then the children at byte 48");
+
+__device__ inline Box box_of_node(int v, int n, const int2* __restrict__ range, const Box* __restrict__ table) {
+  if (v >= n - 1) return table[v - (n - 1)];
+  const int2 r = range[v];
+  const int m = 31 - __clz(r.y - r.x + 1);
+  const Box* lv = table + (long long)m * n;
+  return box_union(lv[r.x], lv[r.y - (1 << m) + 1]);
+}
+
+__global__ void k_nodes(int n, const int2* __restrict__ child, const int2* __restrict__ range,
+                        const Box* __restrict__ table, Node* __restrict__ node) {
   const int i = blockIdx.x * kCcdBlock + threadIdx.x;
   if (i >= n - 1) return;
-  const int2 r = range[i];
-  const int len = r.y - r.x + 1;
-  const int m = 31 - __clz(len);
-  const Box* lv = table + (long long)m * n;
-  node[i] = box_union(lv[r.x], lv[r.y - (1 << m) + 1]);
+  Node o;
+  o.child = child[i];
+  o.left = box_of_node(o.child.x, n, range, table);
+  o.right = box_of_node(o.child.y, n, range, table);
+  o.pad[0] = o.pad[1] = 0;
+  node[i] = o;
 }
 
 // ------------------------------------------------------------ queries
 
-__device__ inline bool overlap(const Box& a, const float lo[3], const float hi[3]) {
-  return a.lo[0] <= hi[0] && lo[0] <= a.hi[0] && a.lo[1] <= hi[1] && lo[1] <= a.hi[1] && a.lo[2] <= hi[2] &&
-         lo[2] <= a.hi[2];
+// (all six comparisons: a short-circuit would wait for one load after another)
+__device__ inline bool overlap(float lx, float ly, float lz, float hx, float hy, float hz, const float lo[3],
+                               const float hi[3]) {
+  return (lx <= hi[0]) & (lo[0] <= hx) & (ly <= hi[1]) & (lo[1] <= hy) & (lz <= hi[2]) & (lo[2] <= hz);
 }
 
 // The oracle's exact test: FP64 swept boxes within delta on every axis.
@@ -338,101 +386,211 @@ __device__ inline bool near_exact(const double alo[3], const double ahi[3], cons
   return ok;
 }
 
-struct QueryOut {
-  int* count;              // [0] colliding pairs, [1] traversal-stack overflow flag, [2..3] candidate count (u64)
-  int cap;
-  int2* pairs;             // (query primitive, tree primitive)
-  double* toc;
+// One thread per query primitive (a surface vertex for PT, an edge for EE), one
+// wavefront per workgroup, in lockstep: every thread walks the tree of the
+// other kind and leaves the leaves it meets in an LDS list (the stack is in
+// LDS too: indexed private arrays live in memory); when the list fills, and at
+// the end, the wavefront takes it through the exact test, kLeafUnroll times 64
+// pairs at a time, and appends those that pass with one atomic.  Testing
+// leaves where they are met would make all lanes wait for each one's loads (20
+// to 30 leaves per query, most of them neighbours that share a vertex), and an
+// atomic per 64 pairs is a round trip each: 154 and 80 us at 2,300 edges,
+// against 61 us.
+constexpr int kLeafCap = 2048;
+constexpr int kLeafUnroll = 4;
+static_assert(kTraverseBlock == kWave, "the wavefront works in lockstep");
+
+struct TraverseLds {
+  int stack[kStackDepth * kTraverseBlock];
+  int leaf[kLeafCap];               // leaf in key order; after the test the tree primitive
+  unsigned char lane[kLeafCap];     // whose query met it
+  double lo[3][kTraverseBlock], hi[3][kTraverseBlock];   // the queries' swept boxes
+  int ids[2][kTraverseBlock];       // and vertices
 };
 
-// One thread per query primitive (a surface vertex for PT, an edge for EE):
-// traverse the tree of the other kind, test the exact condition, run ACCD.
 template <bool kEE>
-__global__ void __launch_bounds__(kCcdBlock)
-k_query(int nq, const int* __restrict__ qids, int nt, const int* __restrict__ tids, const int2* __restrict__ child,
-        const Box* __restrict__ node, const unsigned long long* __restrict__ key, const double* __restrict__ x,
-        const double* __restrict__ xh, double delta, double s, QueryOut out) {
-  const int i = blockIdx.x * kCcdBlock + threadIdx.x;
-  long long cand = 0;
-  if (i < nq && nt > 0) {
-    constexpr int kq = kEE ? 2 : 1;
-    constexpr int kt = kEE ? 2 : 3;
-    int qv[kq];
+__device__ __forceinline__ void test_leaves(int n, int i0, const QuerySide& q, const double* __restrict__ x,
+                                            const double* __restrict__ xh, double delta, int* __restrict__ count,
+                                            TraverseLds& L) {
+  constexpr int kq = kEE ? 2 : 1;
+  constexpr int kt = kEE ? 2 : 3;
+  const int lane = threadIdx.x;
+  const unsigned long long below = (1ull << lane) - 1ull;
+  int kept = 0;
+  __syncthreads();
+  for (int k0 = 0; k0 < n; k0 += kLeafUnroll * kWave) {
+    int j[kLeafUnroll], tv[kLeafUnroll][kt], ql[kLeafUnroll];
+    bool ok[kLeafUnroll];
+    double tlo[kLeafUnroll][3], thi[kLeafUnroll][3];
 #pragma unroll
-    for (int a = 0; a < kq; ++a) qv[a] = qids[(long long)kq * i + a];
-    double qlo[3], qhi[3];
-    box_of(x, xh, qv, kq, qlo, qhi);
-    float flo[3], fhi[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      flo[c] = __double2float_rd(qlo[c] - delta);
-      fhi[c] = __double2float_ru(qhi[c] + delta);
+    for (int u = 0; u < kLeafUnroll; ++u) {
+      const int k = min(k0 + u * kWave + lane, n - 1);
+      ql[u] = L.lane[k];
+      j[u] = (int)(q.key[L.leaf[k]] & 0xffffffffu);
     }
-    int stack[kStackDepth];
-    int sp = 0;
-    stack[sp++] = 0;   // root (a leaf when nt == 1)
-    while (sp > 0) {
-      const int v = stack[--sp];
-      if (!overlap(node[v], flo, fhi)) continue;
-      if (v < nt - 1) {
-        const int2 c = child[v];
-        if (sp + 2 > kStackDepth) {   // cannot happen for trees of depth < 63; reported, never dropped silently
-          out.count[1] = 1;
-          break;
-        }
-        stack[sp++] = c.y;
-        stack[sp++] = c.x;
-        continue;
-      }
-      const int j = (int)(key[v - (nt - 1)] & 0xffffffffu);   // tree primitive index
-      if (kEE && j <= i) continue;
-      int tv[kt];
 #pragma unroll
-      for (int a = 0; a < kt; ++a) tv[a] = tids[(long long)kt * j + a];
-      bool share = false;
+    for (int u = 0; u < kLeafUnroll; ++u)
+#pragma unroll
+      for (int a = 0; a < kt; ++a) tv[u][a] = q.tids[(long long)kt * j[u] + a];
+#pragma unroll
+    for (int u = 0; u < kLeafUnroll; ++u) box_of(x, xh, tv[u], kt, tlo[u], thi[u]);
+#pragma unroll
+    for (int u = 0; u < kLeafUnroll; ++u) {
+      double qlo[3], qhi[3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        qlo[c] = L.lo[c][ql[u]];
+        qhi[c] = L.hi[c][ql[u]];
+      }
+      ok[u] = k0 + u * kWave + lane < n && !(kEE && j[u] <= i0 + ql[u]) &&
+              near_exact(qlo, qhi, tlo[u], thi[u], delta);
 #pragma unroll
       for (int a = 0; a < kq; ++a)
 #pragma unroll
-        for (int b = 0; b < kt; ++b) share = share || qv[a] == tv[b];
-      if (share) continue;
-      double tlo[3], thi[3];
-      box_of(x, xh, tv, kt, tlo, thi);
-      if (!near_exact(qlo, qhi, tlo, thi, delta)) continue;
-      ++cand;
-      int ids[4];
-      if (kEE) {
-        ids[0] = qv[0]; ids[1] = qv[1]; ids[2] = tv[0]; ids[3] = tv[1];
-      } else {
-        ids[0] = qv[0]; ids[1] = tv[0]; ids[2] = tv[1]; ids[3] = tv[2];
-      }
-      d3 X0[4], X1[4];
+        for (int b = 0; b < kt; ++b) ok[u] = ok[u] && L.ids[a][ql[u]] != tv[u][b];
+    }
+    // keep the survivors at the front of the list (every entry of this round has been read)
+    __syncthreads();
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        X0[a] = ld3(x, ids[a]);
-        X1[a] = ld3(xh, ids[a]);
+    for (int u = 0; u < kLeafUnroll; ++u) {
+      const unsigned long long mask = __ballot(ok[u]);
+      if (ok[u]) {
+        const int p = kept + __popcll(mask & below);
+        L.leaf[p] = j[u];
+        L.lane[p] = (unsigned char)ql[u];
       }
-      const double t = accd<kEE>(X0, X1, s);
-      if (t >= 0.0) {
-        const int slot = atomicAdd(out.count, 1);
-        if (slot < out.cap) {
-          out.pairs[slot] = make_int2(i, j);
-          out.toc[slot] = t;
-        }
-      }
+      kept += __popcll(mask);
+    }
+    __syncthreads();
+  }
+  if (kept == 0) return;
+  unsigned long long base = 0;
+  if (lane == 0)
+    base = atomicAdd(reinterpret_cast<unsigned long long*>(count + 2), (unsigned long long)kept);
+  base = __shfl(base, 0, kWave);
+  for (int k = lane; k < kept; k += kWave)
+    if (base + k < (unsigned long long)q.cand_cap) q.cand[base + k] = make_int2(i0 + L.lane[k], L.leaf[k]);
+  __syncthreads();
+}
+
+template <bool kEE>
+__device__ __forceinline__ void traverse(int i0, const QuerySide& q, const double* __restrict__ x,
+                                         const double* __restrict__ xh, double delta, int* __restrict__ count,
+                                         TraverseLds& L) {
+  constexpr int kq = kEE ? 2 : 1;
+  if (q.nt <= 0) return;
+  const Node* __restrict__ node = static_cast<const Node*>(q.node);
+  const int lane = threadIdx.x, i = i0 + lane;
+  const unsigned long long below = (1ull << lane) - 1ull;
+  const bool mine = i < q.nq;
+  int qv[kq];
+#pragma unroll
+  for (int a = 0; a < kq; ++a) {
+    qv[a] = q.qids[(long long)kq * min(i, q.nq - 1) + a];
+    L.ids[a][lane] = qv[a];
+  }
+  double qlo[3], qhi[3];
+  box_of(x, xh, qv, kq, qlo, qhi);
+  float flo[3], fhi[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    L.lo[c][lane] = qlo[c];
+    L.hi[c][lane] = qhi[c];
+    flo[c] = __double2float_rd(qlo[c] - delta);
+    fhi[c] = __double2float_ru(qhi[c] + delta);
+  }
+  int* stack = L.stack + lane;
+  int sp = 0, n = 0;
+  bool overflow = false;
+  auto meet = [&](bool is, int k) {   // leaf k in key order
+    const unsigned long long mask = __ballot(is);
+    if (is) {
+      const int p = n + __popcll(mask & below);
+      L.leaf[p] = k;
+      L.lane[p] = (unsigned char)lane;
+    }
+    n += __popcll(mask);
+  };
+  int v = mine ? 0 : -1;
+  if (q.nt == 1) {
+    meet(mine, 0);
+    v = -1;
+  }
+  while (__any(v >= 0)) {
+    const float4* nd = reinterpret_cast<const float4*>(node + max(v, 0));
+    const float4 n0 = nd[0], n1 = nd[1], n2 = nd[2], n3 = nd[3];
+    const int cl = __float_as_int(n3.x), cr = __float_as_int(n3.y);
+    const bool hl = (v >= 0) & overlap(n0.x, n0.y, n0.z, n0.w, n1.x, n1.y, flo, fhi);
+    const bool hr = (v >= 0) & overlap(n1.z, n1.w, n2.x, n2.y, n2.z, n2.w, flo, fhi);
+    const bool ll = hl & (cl >= q.nt - 1), lr = hr & (cr >= q.nt - 1);
+    if (n > kLeafCap - 2 * kWave) {
+      test_leaves<kEE>(n, i0, q, x, xh, delta, count, L);
+      n = 0;
+    }
+    meet(ll, cl - (q.nt - 1));
+    meet(lr, cr - (q.nt - 1));
+    const int a = hl & !ll ? cl : -1, b = hr & !lr ? cr : -1;
+    if ((a >= 0) & (b >= 0)) {
+      if (sp < kStackDepth) stack[kTraverseBlock * sp++] = b;
+      else overflow = true;   // cannot happen for trees of depth < 63; reported, never dropped silently
+    }
+    v = a >= 0 ? a : b >= 0 ? b : sp > 0 && v >= 0 ? stack[kTraverseBlock * --sp] : -1;
+  }
+  if (overflow) count[1] = 1;
+  if (n) test_leaves<kEE>(n, i0, q, x, xh, delta, count, L);
+}
+
+__global__ void __launch_bounds__(kTraverseBlock)
+k_traverse(QuerySide pt, QuerySide ee, int pt_groups, const double* __restrict__ x, const double* __restrict__ xh,
+           double delta, int* __restrict__ count) {
+  __shared__ TraverseLds L;
+  const int b = blockIdx.x;
+  if (b < pt_groups)
+    traverse<false>(b * kTraverseBlock, pt, x, xh, delta, count, L);
+  else
+    traverse<true>((b - pt_groups) * kTraverseBlock, ee, x, xh, delta, count + 8, L);
+}
+
+// The narrow phase, one thread per candidate of either kind (grid-stride over
+// the lists, whose lengths only the device knows).
+template <bool kEE>
+__device__ __forceinline__ void narrow(const QuerySide& q, int2 pr, const double* __restrict__ x,
+                                       const double* __restrict__ xh, double s, int* __restrict__ count) {
+  int ids[4];
+  if (kEE) {
+    ids[0] = q.qids[2LL * pr.x];
+    ids[1] = q.qids[2LL * pr.x + 1];
+    ids[2] = q.tids[2LL * pr.y];
+    ids[3] = q.tids[2LL * pr.y + 1];
+  } else {
+    ids[0] = q.qids[pr.x];
+    ids[1] = q.tids[3LL * pr.y];
+    ids[2] = q.tids[3LL * pr.y + 1];
+    ids[3] = q.tids[3LL * pr.y + 2];
+  }
+  d3 X0[4], X1[4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    X0[a] = ld3(x, ids[a]);
+    X1[a] = ld3(xh, ids[a]);
+  }
+  const double t = accd<kEE>(X0, X1, s);
+  if (t >= 0.0) {
+    const int slot = atomicAdd(count, 1);
+    if (slot < q.cap) {
+      q.pairs[slot] = pr;
+      q.toc[slot] = t;
     }
   }
-  // candidate count of the workgroup (statistics)
-  __shared__ long long red[kCcdBlock / kWave];
-  long long c = cand;
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) c += __shfl_xor(c, off, kWave);
-  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = c;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    long long tot = 0;
-    for (int w = 0; w < kCcdBlock / kWave; ++w) tot += red[w];
-    if (tot) atomicAdd(reinterpret_cast<unsigned long long*>(out.count + 2), (unsigned long long)tot);
-  }
+}
+
+template <bool kEE>
+__global__ void __launch_bounds__(kNarrowBlock)
+k_narrow(QuerySide q, const double* __restrict__ x, const double* __restrict__ xh, double s, int* __restrict__ count) {
+  const long long total = *reinterpret_cast<const unsigned long long*>(count + 2);
+  const long long n = total < q.cand_cap ? total : q.cand_cap;
+  for (long long k = (long long)blockIdx.x * kNarrowBlock + threadIdx.x; k < n; k += (long long)gridDim.x * kNarrowBlock)
+    narrow<kEE>(q, q.cand[k], x, xh, s, count);
 }
 
 // Canonical 64-bit order of a colliding pair: query index above tree index
@@ -747,7 +905,7 @@ void launch_build_tree(int n, const unsigned long long* key, const void* pbox, i
   if (n <= 0) return;
   Box* T = static_cast<Box*>(table);
   hipLaunchKernelGGL(k_leaf_boxes, dim3(div_up(n, kCcdBlock)), dim3(kCcdBlock), 0, s, n, key,
-                     static_cast<const Box*>(pbox), T, static_cast<Box*>(node));
+                     static_cast<const Box*>(pbox), T);
   if (n == 1) return;
   hipLaunchKernelGGL(k_karras, dim3(div_up(n - 1, kCcdBlock)), dim3(kCcdBlock), 0, s, n, key, child, range);
   const int L = ccd_table_levels(n);
@@ -756,21 +914,23 @@ void launch_build_tree(int n, const unsigned long long* key, const void* pbox, i
     hipLaunchKernelGGL(k_sparse_level, dim3(div_up(n - 2 * h + 1, kCcdBlock)), dim3(kCcdBlock), 0, s, n, h,
                        T + (long long)(k - 1) * n, T + (long long)k * n);
   }
-  hipLaunchKernelGGL(k_node_boxes, dim3(div_up(n - 1, kCcdBlock)), dim3(kCcdBlock), 0, s, n, range, T,
-                     static_cast<Box*>(node));
+  hipLaunchKernelGGL(k_nodes, dim3(div_up(n - 1, kCcdBlock)), dim3(kCcdBlock), 0, s, n, (const int2*)child,
+                     (const int2*)range, (const Box*)T, static_cast<Node*>(node));
 }
 
-void launch_query(bool ee, int nq, const int* qids, int nt, const int* tids, const int2* child, const void* node,
-                  const unsigned long long* key, const double* x, const double* xh, double delta, double sep,
-                  int* count, int cap, int2* pairs, double* toc, hipStream_t s) {
-  if (nq <= 0) return;
-  QueryOut out{count, cap, pairs, toc};
-  if (ee)
-    hipLaunchKernelGGL(k_query<true>, dim3(div_up(nq, kCcdBlock)), dim3(kCcdBlock), 0, s, nq, qids, nt, tids, child,
-                       static_cast<const Box*>(node), key, x, xh, delta, sep, out);
-  else
-    hipLaunchKernelGGL(k_query<false>, dim3(div_up(nq, kCcdBlock)), dim3(kCcdBlock), 0, s, nq, qids, nt, tids, child,
-                       static_cast<const Box*>(node), key, x, xh, delta, sep, out);
+size_t ccd_node_bytes(int n) { return sizeof(Node) * std::max(n - 1, 1); }
+
+void launch_queries(const QuerySide& pt, const QuerySide& ee, bool do_pt, bool do_ee, const double* x, const double* xh,
+                    double delta, double sep, int* count, hipStream_t s) {
+  const int gp = do_pt ? div_up(pt.nq, kTraverseBlock) : 0, ge = do_ee ? div_up(ee.nq, kTraverseBlock) : 0;
+  if (gp + ge)
+    hipLaunchKernelGGL(k_traverse, dim3(gp + ge), dim3(kTraverseBlock), 0, s, pt, ee, gp, x, xh, delta, count);
+  // 16 wavefronts per compute unit: the lists are walked with a stride
+  const int grid = 256 * 16;
+  if (gp)
+    hipLaunchKernelGGL(k_narrow<false>, dim3(grid), dim3(kNarrowBlock), 0, s, pt, x, xh, sep, count);
+  if (ge)
+    hipLaunchKernelGGL(k_narrow<true>, dim3(grid), dim3(kNarrowBlock), 0, s, ee, x, xh, sep, count + 8);
 }
 
 void launch_pair_keys(int n, const int2* pairs, unsigned long long* key, int* idx, hipStream_t s) {

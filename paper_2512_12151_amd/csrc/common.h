@@ -239,9 +239,26 @@ void launch_morton(int n, const void* box, void* part, unsigned long long* key, 
 int ccd_table_levels(int n);
 void launch_build_tree(int n, const unsigned long long* key, const void* pbox, int2* child, int2* range, void* node,
                        void* table, hipStream_t s);
-void launch_query(bool ee, int nq, const int* qids, int nt, const int* tids, const int2* child, const void* node,
-                  const unsigned long long* key, const double* x, const double* xh, double delta, double sep,
-                  int* count, int cap, int2* pairs, double* toc, hipStream_t s);
+size_t ccd_node_bytes(int n);   // node storage of a tree over n primitives
+// One kind of query: its primitives, the tree they meet, the candidate list
+// (pairs within delta: query index, tree index) and the colliding pairs.
+struct QuerySide {
+  int nq, nt;
+  const int* qids;
+  const int* tids;
+  const void* node;
+  const unsigned long long* key;
+  int2* cand;
+  long long cand_cap;
+  int2* pairs;
+  double* toc;
+  int cap;
+};
+// Both kinds in one traversal and their narrow phases.  count holds eight ints
+// per kind, zeroed: [0] colliding pairs, [1] stack overflow flag, [2..3]
+// candidates (64 bits); counts beyond a list's room say how much was wanted.
+void launch_queries(const QuerySide& pt, const QuerySide& ee, bool do_pt, bool do_ee, const double* x, const double* xh,
+                    double delta, double sep, int* count, hipStream_t s);
 void launch_pair_keys(int n, const int2* pairs, unsigned long long* key, int* idx, hipStream_t s);
 void launch_hash_insert(int n_c, int n_pt, const int4* ids, int* table, unsigned int mask, hipStream_t s);
 void launch_fill_u64(unsigned long long* a, unsigned long long v, int n, hipStream_t s);

@@ -70,6 +70,8 @@ struct bf_problem {
   DevBuf htable, tvmin, keepn[2], posn[2], keepc, posc, nids, nlam, ngam, mpart;
   DevBuf xstart, xprev, vout;   // time step: x^t, the subproblem's input x_hat, the velocity
   int qcap[2] = {0, 0};
+  DevBuf qcand[2];         // candidate pairs of the queries
+  long long ccap[2] = {0, 0};
   int qhits[2] = {0, 0};   // colliding pairs of the last collision call (-1: none yet)
   bool collided = false;
   bool stepped = false;

@@ -253,3 +253,28 @@ def test_inversion_bound_either_orientation(ctx, bf):
     assert 0.0 < ref < 1.0
     for a in alphas.values():
         assert a == pytest.approx(ref, rel=1e-8)
+
+
+@pytest.mark.parametrize("delta,n", [(0.02, 4), (0.6, 4), (0.15, 7)])
+def test_many_candidates_per_query_match_oracle(ctx, bf, delta, n):
+    """A wide separation offset makes most of the surface a candidate of every
+    query (up to 75,000 point-triangle pairs from 196 vertices): the leaf lists
+    of the traversal fill and are emptied on the way, and the candidate list is
+    found too small and asked for again."""
+    sc = dict(scenes.tiny(n=n, lateral=(0.37, 0.21)))
+    sc["delta"] = delta
+    xh = scenes.ccd_target(sc, "push")
+    tris, edges, verts = ccd.surface(sc["tets"])
+    pt, ee = ccd.candidates(sc["x"], xh, tris, edges, verts, delta)
+    (cpt, tpt), (cee, tee) = ccd.colliding_pairs(sc["x"], xh, tris, edges, verts, delta)
+    pb = bf.Problem.from_scene(ctx, sc)
+    for _ in range(2):   # the second call finds the lists large enough
+        _, st = pb.max_step_size(xh)
+        assert (st["candidates_pt"], st["candidates_ee"]) == (len(pt), len(ee))
+        assert (st["colliding_pt"], st["colliding_ee"]) == (len(cpt), len(cee))
+        gpt, gtp, gee, gte = pb.collisions(st)
+        for g_rows, g_t, o_rows, o_t in ((gpt, gtp, cpt, tpt), (gee, gte, cee, tee)):
+            g_rows, g_t = _by_row(g_rows.astype(np.int64), g_t)
+            o_rows, o_t = _by_row(o_rows.astype(np.int64), o_t)
+            assert np.array_equal(g_rows, o_rows)
+            assert np.allclose(g_t, o_t, rtol=1e-8, atol=1e-15)
