@@ -110,9 +110,8 @@ typedef struct {
   int32_t poll_every;    /* host polls the device convergence flag every this many iterations (systems of
                             up to 32,768 nodes report their end to the host by themselves) */
   int32_t check_every;   /* the true residual norm is formed every this many iterations */
-  int32_t time_spmv;     /* >0: time the SpMV launches (below 32,769 nodes: the iteration's one launch) of
-                            the first this-many PCG iterations
-                            with HIP events (reported in bf_step_stats); 0: no per-kernel events */
+  int32_t time_spmv;     /* >0: time the SpMV launches (below 32,769 nodes: the iteration's one launch; iterations
+                            that are not timed need none) of the first this-many PCG iterations with HIP events (reported in bf_step_stats); 0: no per-kernel events */
   int32_t max_sweeps;    /* BF16 mode: at most this many inner solves (0 means 100) */
 } bf_solve_opts;
 

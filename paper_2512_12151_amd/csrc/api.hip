@@ -170,7 +170,7 @@ bf_status problem_init(bf_context* c, bf_problem* pb, const bf_mesh_desc* m, int
     if (!e) HIPCHK(c, hipEventCreate(&e));
   if (!pb->host_sc) {
     static_assert(sizeof(PcgScalars) % sizeof(unsigned long long) == 0, "host_stat follows the scalars");
-    HIPCHK(c, hipHostMalloc((void**)&pb->host_sc, sizeof(PcgScalars) + 2 * sizeof(unsigned long long), hipHostMallocDefault));
+    HIPCHK(c, hipHostMalloc((void**)&pb->host_sc, sizeof(PcgScalars) + 3 * sizeof(unsigned long long), hipHostMallocDefault));
     pb->host_stat = reinterpret_cast<unsigned long long*>(pb->host_sc + 1);
   }
   ALLOC(c, pb->scal, sizeof(PcgScalars));
@@ -611,7 +611,7 @@ bf_status size_constraint_buffers(bf_problem* pb, int n_pt, int n_ee) {
   for (DevBuf* b : {&pb->Lf, &pb->Linv, &pb->bhat, &pb->xs, &pb->rd, &pb->r, &pb->pring, &pb->q})
     HIPCHK(c, hipMemsetAsync(b->p, 0, b->bytes, s));
   HIPCHK(c, hipStreamSynchronize(s));
-  ALLOC(c, pb->part, 8LL * kPartsPerSystem);
+  ALLOC(c, pb->part, 8LL * (pcg_fused_groups(N) ? kResidentParts : kPartsPerSystem));
   ALLOC(c, pb->pout, 24LL * N);
   ALLOC(c, pb->scan_tmp, 4LL * scan_tmp_ints((long long)10 * pb->T + N + 6LL * np + 16));
   pb->cap_nnzb = cap;
@@ -659,29 +659,45 @@ bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* o, double* p_out, 
   }
   int launched = 0, total_iters = 0, timed = 0, replacements = 0;
   bool assembly_checked = false;
-  // A one-kernel solve: kept kFusedAhead launches ahead of what the device has
-  // reported into pinned memory (every fourth launch, and its end), so that
-  // neither side waits and few launches follow the end.  Sets host_sc->iter.
-  constexpr int kFusedAhead = 12;
+  // A one-kernel solve: kept some launches ahead of what the device has
+  // reported into pinned memory, so that neither side waits and few launches
+  // follow the end.  Sets host_sc->iter.  Where the system's workgroups fit the
+  // chip the launches are, in turn, the state that starts a solve, as many
+  // steps as there are up to a replacement, and the replacement: each does
+  // nothing where the state is another's.  Launches that are timed, and a
+  // solve whose workgroups did not get the chip to themselves, take one
+  // iteration each.
+  constexpr int kFusedAhead = 12, kResidentAhead = 4, kResidentSteps = 4096;
   auto run_fused = [&](PcgSystem Sx, bool use_bf16) -> bf_status {
     volatile unsigned long long* st = pb->host_stat;
-    st[0] = st[1] = 0;
+    st[0] = st[1] = st[2] = 0;
     Sx.hstat = pb->host_stat;
+    bool res = pcg_resident(Sx, c->num_cu);
     long long mine = 0, spins = 0;
     for (;;) {
       const unsigned long long w = st[0];
-      if (w & 0xffffffffu) {
-        if ((w & 0xffffffffu) == kEndAssembly) {
+      const unsigned end = (unsigned)(w & 0xffffffffu);
+      if (end) {
+        if (end == kEndAssembly) {
           int hf = 0;
           bf_status r0 = read_flags(pb, &hf);
           return r0 != BF_OK ? r0 : flags_to_status(c, hf);
         }
+        if (end == kEndStuck) {
+          (void)hipStreamSynchronize(s);
+          return fail(c, BF_ERR_HIP, "the solve's workgroups lost each other");
+        }
         break;
       }
-      if (mine - (long long)(w >> 32) < kFusedAhead) {
+      if (res && st[2]) res = false;
+      if (mine - (long long)(w >> 32) < (res ? kResidentAhead : kFusedAhead)) {
         const bool t = launched < ntime;
-        launch_pcg_fused(Sx, use_bf16, (int)(mine & 1), s, t ? pb->tev[2 * launched] : nullptr,
-                         t ? pb->tev[2 * launched + 1] : nullptr);
+        Sx.report_mask = res ? 0 : 3;
+        if (res && !t && mine % 3 == 1)
+          launch_pcg_resident(Sx, use_bf16, (int)(mine & 1), kResidentSteps, s);
+        else
+          launch_pcg_fused(Sx, use_bf16, (int)(mine & 1), s, t ? pb->tev[2 * launched] : nullptr,
+                           t ? pb->tev[2 * launched + 1] : nullptr);
         if (mine == 0) HIPCHK(c, hipGetLastError());
         ++launched;
         ++mine;

@@ -30,7 +30,7 @@ constexpr int kBlock = 256;        // default workgroup size (4 waves)
 // State of a one-kernel PCG solve between launches (pcg_fused.hip).
 enum : int { kNormal = 0, kTested = 1, kFresh = 2, kReplace = 3 };
 // How a one-kernel solve ended; the first two are the values of PcgScalars::done.
-enum : int { kEndConverged = 1, kEndMaxIter = 2, kEndBreakdown = 8, kEndAssembly = 16 };
+enum : int { kEndConverged = 1, kEndMaxIter = 2, kEndBreakdown = 8, kEndAssembly = 16, kEndStuck = 32 };
 struct PcgCtl {
   int k;             // iteration of the state
   int mode;          // kNormal, kTested, kFresh or kReplace
@@ -40,7 +40,7 @@ struct PcgCtl {
   // the solve's parameters, carried along so that a launch finds all it needs in one place
   int every, max_iter, replace_on;
   int phase;         // k modulo every: 0 where |L r| is tested
-  int pad;
+  int apart;         // 1: the resident kernel found its workgroups not all running, launches go on alone
   double rho_prev;   // r^T r of iteration k - 1
   double rt_ref;     // |L r|^2 right after the last residual replacement (or |b|^2)
   double tol_bb;     // tol^2 |b|^2
@@ -89,6 +89,11 @@ constexpr int kPartPQ = 3 * kMaxVecParts;               // p^T H p
 constexpr int kPartRQ = kPartPQ + kMaxSpmvParts;        // r^T H p
 constexpr int kPartQQ = kPartRQ + kMaxSpmvParts;        // |H p|^2
 constexpr int kPartsPerSystem = 6144;   // the two-kernel iteration's, or the one-kernel iteration's
+// The resident kernel's (pcg_fused.hip), behind them: tagged sums of 16 bytes,
+// five per slice for two iterations, their totals in some copies, one line
+// each, and its start words.
+constexpr int kTotalBytes = 128, kTotalCopies = 8;
+constexpr int kStartWords = 64;        // 4-byte words, for two launches
 static_assert(kPartQQ + kMaxSpmvParts <= kPartsPerSystem, "they fit");
 
 constexpr int kSlice = 64;         // rows per slice of the sliced block storage (one wavefront)
@@ -98,6 +103,8 @@ constexpr int kSlice = 64;         // rows per slice of the sliced block storage
 // and two of a replaced residual.
 constexpr int kFusedMaxSlices = 512;
 static_assert((2 * 5 + 2) * kFusedMaxSlices <= kPartsPerSystem, "they fit the partials");
+constexpr int kTaggedParts = 2 * 2 * 5 * kFusedMaxSlices + 2 * kTotalCopies * kTotalBytes / 8;   // doubles
+constexpr int kResidentParts = kPartsPerSystem + kTaggedParts + kStartWords;
 
 // One symmetric block system of the PCG, H_hat = L^{-1} H L^{-T} with identity
 // diagonal blocks, in sliced storage (kSlice consecutive rows per slice, slot k
@@ -125,7 +132,7 @@ struct PcgSystem {
   float* P;          // ring of kPRing direction buffers: p_k at P + (k % kPRing) * pstride
   long long pstride; // floats per direction buffer (3 N4)
   float* q;
-  double* part;      // kPartsPerSystem
+  double* part;      // kPartsPerSystem, or kResidentParts where fused_nwg > 0
   PcgScalars* sc;
   int spmv_wg0, spmv_nwg;
   int vec_wg0, vec_nwg;
@@ -134,8 +141,14 @@ struct PcgSystem {
   int fused_wg0, fused_nwg;
   const float* bhat;
   const int* aflags;             // the assembly's error flags, or null
-  unsigned long long* hstat;     // pinned host words: launches << 32 | end code, iteration of the end; or null
+  unsigned long long* hstat;     // pinned host words: launches << 32 | end code, iteration of the end, PcgCtl::apart; or null
+  int report_mask;               // launches with (number & mask) == 0 report, and the end does
 };
+
+// The start words of a one-kernel system (null: the two kernels take it).
+__host__ __device__ inline unsigned* resident_start(const PcgSystem& S) {
+  return S.fused_nwg ? reinterpret_cast<unsigned*>(S.part + kPartsPerSystem + kTaggedParts) : nullptr;
+}
 
 __host__ __device__ inline int div_up(long long a, long long b) { return (int)((a + b - 1) / b); }
 
@@ -372,6 +385,11 @@ void launch_pcg_iteration_batched(const PcgSystem* sys, const int* wg_sys_spmv, 
 int pcg_fused_groups(int N);
 void launch_pcg_fused(const PcgSystem& S, bool bf16, int par, hipStream_t s, hipEvent_t t0 = nullptr,
                       hipEvent_t t1 = nullptr);
+// The resident form: one launch that makes up to `steps` iterations of a solve
+// whose workgroups all fit the chip (pcg_resident).  It leaves the states that
+// start, resume or replace a residual to launch_pcg_fused.
+bool pcg_resident(const PcgSystem& S, int num_cu);
+void launch_pcg_resident(const PcgSystem& S, bool bf16, int par, int steps, hipStream_t s);
 void launch_pcg_fused_batched(const PcgSystem* sys, const int* wg_sys, int nwg, int par, hipStream_t s);
 // x += the directions the update kernel has not applied yet (before x is read).
 void launch_pcg_flush(const PcgSystem& S, hipStream_t s);

@@ -683,7 +683,8 @@ k_init(int n3, const float* __restrict__ bhat, double* __restrict__ x, float* __
 
 __global__ void __launch_bounds__(kBlock)
 k_init_scalars(const double* __restrict__ bb_part, int nbb, PcgScalars* sc, double tol, int max_iter,
-               int check_every, int replace) {
+               int check_every, int replace, unsigned* start) {
+  if (start && threadIdx.x < kStartWords) start[threadIdx.x] = 0;   // the resident kernel's
   const double bb = sum_parts<kBlock>(bb_part, nbb);
   if (threadIdx.x == 0) {
     sc->rt_ref = bb;
@@ -710,7 +711,7 @@ k_init_scalars(const double* __restrict__ bb_part, int nbb, PcgScalars* sc, doub
     c.every = sc->check_every;
     c.max_iter = max_iter;
     c.replace_on = replace;
-    c.phase = c.pad = 0;
+    c.phase = c.apart = 0;
     c.rho_prev = 0.0;
     c.rt_ref = bb;
     c.tol_bb = sc->tol2 * bb;
@@ -957,7 +958,7 @@ void launch_pcg_init(const PcgSystem& S, const float* bhat, const double* bb_par
                      int check_every, bool replace, hipStream_t s) {
   hipLaunchKernelGGL(k_init, dim3(S.vec_nwg), dim3(kVecBlock), 0, s, 3 * S.N4, bhat, S.x, S.r, S.P, S.part);
   hipLaunchKernelGGL(k_init_scalars, dim3(1), dim3(kBlock), 0, s, bb_part, nbb, S.sc, tol, max_iter, check_every,
-                     replace ? 1 : 0);
+                     replace ? 1 : 0, resident_start(S));
 }
 
 void launch_pcg_flush(const PcgSystem& S, hipStream_t s) {
@@ -1013,7 +1014,7 @@ void launch_pcg_init_from64(const PcgSystem& S, const double* rd, const double* 
                             int max_iter, int check_every, hipStream_t s) {
   hipLaunchKernelGGL(k_init_from64, dim3(S.vec_nwg), dim3(kVecBlock), 0, s, 3 * S.N4, rd, S.x, S.r, S.P, S.part);
   hipLaunchKernelGGL(k_init_scalars, dim3(1), dim3(kBlock), 0, s, rpart, nparts, S.sc, tol, max_iter, check_every,
-                     0);
+                     0, resident_start(S));
 }
 
 void launch_residual64(const PcgSystem& S, const float* bhat, const double* xd, double* rd, double* rpart,

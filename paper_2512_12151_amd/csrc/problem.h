@@ -155,6 +155,7 @@ inline PcgSystem system_of(bf_problem* pb) {
   S.bhat = pb->bhat.as<float>();
   S.aflags = pb->flags.as<int>();
   S.hstat = nullptr;
+  S.report_mask = 3;
   return S;
 }
 

@@ -25,7 +25,6 @@ __device__ __forceinline__ double dpp_move(double v) {
 constexpr int kDppRowRor8 = 0x128, kDppRowRor4 = 0x124;
 constexpr int kDppQuadXor2 = 0x4e;   // lanes 2, 3, 0, 1
 constexpr int kDppQuadXor1 = 0xb1;   // lanes 1, 0, 3, 2
-constexpr int kDppHalfMirror = 0x141;   // lane 7 - i of each 8
 
 __device__ __forceinline__ double wave_sum_all(double v) {
   {

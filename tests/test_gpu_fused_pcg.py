@@ -117,3 +117,60 @@ def test_batched_solves_equal_the_same_solves_alone():
                 i = left.pop(q)
                 assert status == 0 and np.array_equal(p, alone[i]), f"round {rep}, request {i} ({len(p)} nodes)"
     srv.close()
+
+
+RESIDENT = [
+    ("63 rows", lambda: _box(2, 2, 6)),
+    ("130 rows", lambda: _box(12, 4, 1)),
+    ("wide rows", _crowded),
+    ("507 slices", lambda: _box(31, 38, 25)),            # 32,448 rows: the largest whose workgroups fit the chip
+    ("508 slices", lambda: _box(126, 15, 15)),           # 32,512 rows: by launches
+]
+
+
+@pytest.mark.parametrize("name,make", RESIDENT, ids=[c[0] for c in RESIDENT])
+@pytest.mark.parametrize("check_every", [1, 5])
+def test_resident_iterations_equal_launched_ones(name, make, check_every):
+    """Timed iterations are launches of their own, the others stay in one
+    kernel: the same solve both ways, replacements included, bit for bit, and
+    with the change from one to the other at every kind of state."""
+    pb = bfal.Problem.from_scene(bfal.Context(0), make())
+    opts = dict(tol=1e-9, check_every=check_every, max_iter=3000)
+    p, st, status = pb.newton_step(time_spmv=4096, **opts)
+    for timed in (0, 0, 1, 2, 3, 50):
+        q, su, status2 = pb.newton_step(time_spmv=timed, **opts)
+        print(name, timed, st["pcg_iters"], su["pcg_iters"], flush=True)
+        assert status == status2 and st["pcg_iters"] == su["pcg_iters"]
+        assert np.array_equal(p, q) and st["rel_residual"] == su["rel_residual"]
+
+
+def test_resident_bf16_refinement_equals_launched():
+    pb = bfal.Problem.from_scene(bfal.Context(0), _crowded())
+    opts = dict(tol=0.05, refine_tol=1e-6, precision=bfal.BF_PREC_BF16_REFINE)
+    p, st, status = pb.newton_step(time_spmv=4096, **opts)
+    q, su, status2 = pb.newton_step(**opts)
+    assert status == status2 == 0 and st["pcg_iters"] == su["pcg_iters"] and np.array_equal(p, q)
+
+
+def test_solves_side_by_side_equal_the_same_solves_alone():
+    """Threads with a context each, whose workgroups do not all fit the chip
+    together: solves that find no room for all of theirs go on by launches."""
+    import threading
+    sc = _box(31, 31, 25)   # 26,624 rows: 416 slices
+    p, _, _ = bfal.Problem.from_scene(bfal.Context(0), sc).newton_step(tol=1e-7)
+    bad = []
+
+    def work():
+        pb = bfal.Problem.from_scene(bfal.Context(0), sc)
+        for _ in range(4):
+            q, _, status = pb.newton_step(tol=1e-7)
+            if status != 0 or not np.array_equal(p, q):
+                bad.append(status)
+
+    ts = [threading.Thread(target=work) for _ in range(4)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join(100)
+        assert not t.is_alive()
+    assert not bad
