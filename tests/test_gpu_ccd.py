@@ -278,3 +278,10 @@ def test_many_candidates_per_query_match_oracle(ctx, bf, delta, n):
             o_rows, o_t = _by_row(o_rows.astype(np.int64), o_t)
             assert np.array_equal(g_rows, o_rows)
             assert np.allclose(g_t, o_t, rtol=1e-8, atol=1e-15)
+
+
+@pytest.mark.parametrize("n", [2, 3, 5])
+def test_small_trees_match_oracle(ctx, bf, n):
+    """Trees of 96 to 900 leaves: the table of node boxes has 7 to 10 levels,
+    so the last launch that builds it makes one, two, three or four of them."""
+    test_many_candidates_per_query_match_oracle(ctx, bf, 0.3, n)
