@@ -170,8 +170,9 @@ bf_status problem_init(bf_context* c, bf_problem* pb, const bf_mesh_desc* m, int
     if (!e) HIPCHK(c, hipEventCreate(&e));
   if (!pb->host_sc) {
     static_assert(sizeof(PcgScalars) % sizeof(unsigned long long) == 0, "host_stat follows the scalars");
-    HIPCHK(c, hipHostMalloc((void**)&pb->host_sc, sizeof(PcgScalars) + 3 * sizeof(unsigned long long), hipHostMallocDefault));
+    HIPCHK(c, hipHostMalloc((void**)&pb->host_sc, sizeof(PcgScalars) + 5 * sizeof(unsigned long long), hipHostMallocDefault));
     pb->host_stat = reinterpret_cast<unsigned long long*>(pb->host_sc + 1);
+    pb->host_slots = reinterpret_cast<int*>(pb->host_stat + 3);
   }
   ALLOC(c, pb->scal, sizeof(PcgScalars));
   HIPCHK(c, hipMemsetAsync(pb->scal.p, 0, sizeof(PcgScalars), s));
@@ -193,10 +194,20 @@ bf_status step_assemble(bf_problem* pb, bool bf16) {
   const int4* ids = pb->cids.as<int4>();
   const int4* pids = ids;   // the pattern's stencils
   int npat = n;
-  fill_int(flags, 0, 16, s);
+  int* vcnt = pb->vcnt.as<int>();
+  int* lcnt = pb->lcnt.as<int>();
+  int* wmax = pb->scratch_int.as<int>();   // free after the per-mesh setup
+  {
+    ZeroList z;
+    z.add(flags, 4 * 16);
+    z.add(pb->viol_part.p, 4 * 2);
+    z.add(vcnt, 4LL * N);
+    z.add(lcnt, 4LL * N);
+    z.add(wmax, 4 * 2);
+    zero_many(z, s);
+  }
   HIPCHK(c, hipEventRecord(pb->ev[0], s));
   // (1) constraint linearization at x and AL factors at x_hat
-  fill_int(reinterpret_cast<int*>(pb->viol_part.p), 0, 2, s);
   launch_contact_lin(ids, pb->n_pt, n, pb->x.as<double>(), pb->xh.as<double>(), pb->clam.as<double>(),
                      pb->cgam.as<double>(), pb->kappa, pb->delta, pb->cg.as<double>(), pb->ch.as<double>(),
                      pb->lin64.as<double>(), pb->viol_part.as<double>(), flags, s);
@@ -222,12 +233,9 @@ bf_status step_assemble(bf_problem* pb, bool bf16) {
     pids = pb->pids.as<int4>();
     npat = n + n_extra;
   }
-  int* vcnt = pb->vcnt.as<int>();
   int* vptr = pb->vptr.as<int>();
-  fill_int(vcnt, 0, N, s);
   launch_vertex_incidence_count(pids, npat, vcnt, s);
   scan_exclusive(vcnt, vptr, N, vptr + N, tmp, s);
-  fill_int(vcnt, 0, N, s);
   launch_vertex_incidence_fill(pids, npat, vptr, vcnt, pb->vinc.as<int>(), s);
   sort_segments(pb->vinc.as<int>(), vptr, N, s);
   int* cptr = pb->cptr.as<int>();
@@ -259,44 +267,65 @@ bf_status step_assemble(bf_problem* pb, bool bf16) {
                        pb->Linv.as<double>(), pb->bhat.as<float>(), pb->bb_part.as<double>(), flags, s);
   // sliced storage of the scaled matrix: per column the source rows of its
   // upper blocks, slot counts per slice, then the slots themselves
-  int* lcnt = pb->lcnt.as<int>();
   int* lptr = pb->lptr.as<int>();
-  fill_int(lcnt, 0, N, s);
   launch_lower_count(N, row_ptr, pb->col.as<int>(), lcnt, s);
   scan_exclusive(lcnt, lptr, N, lptr + N, tmp, s);
-  fill_int(lcnt, 0, N, s);
   launch_lower_fill(N, row_ptr, pb->col.as<int>(), lptr, lcnt, pb->lsrc.as<int>(), s);
   sort_segments(pb->lsrc.as<int>(), lptr, N, s);
   const int nslices = div_up(N, kSlice);
   int* sbu = pb->sbu.as<int>();
   int* sbl = pb->sbl.as<int>();
-  int* wmax = pb->scratch_int.as<int>();   // free after the per-mesh setup
-  fill_int(wmax, 0, 2, s);
-  launch_slice_widths(N, nslices, row_ptr, lptr, sbu, sbl, wmax, s);
-  scan_exclusive(sbu, sbu, nslices, sbu + nslices, tmp, s);
-  scan_exclusive(sbl, sbl, nslices, sbl + nslices, tmp, s);
-  // the slot offsets come to the host for the SpMV's slice plan (bf_slice_plan)
+  // the slots' number and the largest widths come to the host for the arrays'
+  // sizes; for the SpMV's slice plan (bf_slice_plan) the offsets themselves,
+  // where the two-kernel iteration takes the system
   int tot[4] = {0, 0, 0, 0};
-  pb->h_sbu.resize(nslices + 1);
-  pb->h_sbl.resize(nslices + 1);
-  HIPCHK(c, hipMemcpyAsync(pb->h_sbu.data(), sbu, 4LL * (nslices + 1), hipMemcpyDeviceToHost, s));
-  HIPCHK(c, hipMemcpyAsync(pb->h_sbl.data(), sbl, 4LL * (nslices + 1), hipMemcpyDeviceToHost, s));
-  HIPCHK(c, hipMemcpyAsync(&tot[2], wmax, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
-  HIPCHK(c, hipStreamSynchronize(s));
-  tot[0] = pb->h_sbu[nslices];
-  tot[1] = pb->h_sbl[nslices];
+  auto copy_offsets = [&]() -> bf_status {
+    pb->h_sbu.resize(nslices + 1);
+    pb->h_sbl.resize(nslices + 1);
+    HIPCHK(c, hipMemcpyAsync(pb->h_sbu.data(), sbu, 4LL * (nslices + 1), hipMemcpyDeviceToHost, s));
+    HIPCHK(c, hipMemcpyAsync(pb->h_sbl.data(), sbl, 4LL * (nslices + 1), hipMemcpyDeviceToHost, s));
+    return BF_OK;
+  };
+  const bool two_kernels = pcg_fused_groups(N) == 0;
+  if (nslices <= kOffsetSlices) {
+    launch_slice_widths(N, nslices, row_ptr, lptr, sbu, sbl, nullptr, s);
+    launch_slice_offsets(nslices, sbu, sbl, pb->host_slots, s);
+    if (two_kernels) {
+      const bf_status r0 = copy_offsets();
+      if (r0 != BF_OK) return r0;
+    }
+    HIPCHK(c, hipStreamSynchronize(s));
+    for (int k = 0; k < 4; ++k) tot[k] = pb->host_slots[k];
+  } else {
+    launch_slice_widths(N, nslices, row_ptr, lptr, sbu, sbl, wmax, s);
+    scan_exclusive(sbu, sbu, nslices, sbu + nslices, tmp, s);
+    scan_exclusive(sbl, sbl, nslices, sbl + nslices, tmp, s);
+    const bf_status r0 = copy_offsets();
+    if (r0 != BF_OK) return r0;
+    HIPCHK(c, hipMemcpyAsync(&tot[2], wmax, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+    HIPCHK(c, hipStreamSynchronize(s));
+    tot[0] = pb->h_sbu[nslices];
+    tot[1] = pb->h_sbl[nslices];
+  }
   pb->nslot_u = tot[0];
   pb->nslot_l = tot[1];
-  const int nparts = kSpmvWaves * pcg_spmv_groups(N, c->num_cu);
-  pb->h_wptr.resize(nparts + 1);
-  pb->h_wsl.resize(nslices);
-  if (bf_slice_plan(nslices, pb->h_sbu.data(), pb->h_sbl.data(), kPairs, nparts, pb->h_wptr.data(),
-                    pb->h_wsl.data()) != BF_OK)
-    return fail(c, BF_ERR_INVALID_ARG, "the slice plan rejected the slot offsets");
-  ALLOC(c, pb->wplan_ptr, 4LL * (nparts + 1));
-  ALLOC(c, pb->wplan_sl, 4LL * nslices);
-  HIPCHK(c, hipMemcpyAsync(pb->wplan_ptr.p, pb->h_wptr.data(), 4LL * (nparts + 1), hipMemcpyHostToDevice, s));
-  HIPCHK(c, hipMemcpyAsync(pb->wplan_sl.p, pb->h_wsl.data(), 4LL * nslices, hipMemcpyHostToDevice, s));
+  if (!fused_groups(pb)) {
+    if (!two_kernels) {   // more slots than the one-kernel iteration can address
+      const bf_status r0 = copy_offsets();
+      if (r0 != BF_OK) return r0;
+      HIPCHK(c, hipStreamSynchronize(s));
+    }
+    const int nparts = kSpmvWaves * pcg_spmv_groups(N, c->num_cu);
+    pb->h_wptr.resize(nparts + 1);
+    pb->h_wsl.resize(nslices);
+    if (bf_slice_plan(nslices, pb->h_sbu.data(), pb->h_sbl.data(), kPairs, nparts, pb->h_wptr.data(),
+                      pb->h_wsl.data()) != BF_OK)
+      return fail(c, BF_ERR_INVALID_ARG, "the slice plan rejected the slot offsets");
+    ALLOC(c, pb->wplan_ptr, 4LL * (nparts + 1));
+    ALLOC(c, pb->wplan_sl, 4LL * nslices);
+    HIPCHK(c, hipMemcpyAsync(pb->wplan_ptr.p, pb->h_wptr.data(), 4LL * (nparts + 1), hipMemcpyHostToDevice, s));
+    HIPCHK(c, hipMemcpyAsync(pb->wplan_sl.p, pb->h_wsl.data(), 4LL * nslices, hipMemcpyHostToDevice, s));
+  }
   // slot arrays with the zero block (upper) and the SpMV's read-ahead padding
   const long long nu_alloc = tot[0] + slot_padding(tot[3]);
   const long long nl_alloc = tot[1] + slot_padding(tot[2]);
@@ -304,10 +333,14 @@ bf_status step_assemble(bf_problem* pb, bool bf16) {
   if (bf16) ALLOC(c, pb->sblk16, 20LL * nu_alloc);
   ALLOC(c, pb->scol, 4LL * nu_alloc);
   ALLOC(c, pb->sent, 8LL * nl_alloc);
-  HIPCHK(c, hipMemsetAsync(pb->sblk.as<char>() + 36LL * tot[0], 0, 36LL * (nu_alloc - tot[0]), s));
-  if (bf16) HIPCHK(c, hipMemsetAsync(pb->sblk16.as<char>() + 20LL * tot[0], 0, 20LL * (nu_alloc - tot[0]), s));
-  HIPCHK(c, hipMemsetAsync(pb->scol.as<char>() + 4LL * tot[0], 0, 4LL * (nu_alloc - tot[0]), s));
-  HIPCHK(c, hipMemsetAsync(pb->sent.as<char>() + 8LL * tot[1], 0, 8LL * (nl_alloc - tot[1]), s));
+  {
+    ZeroList z;
+    z.add(pb->sblk.as<char>() + 36LL * tot[0], 36LL * (nu_alloc - tot[0]));
+    if (bf16) z.add(pb->sblk16.as<char>() + 20LL * tot[0], 20LL * (nu_alloc - tot[0]));
+    z.add(pb->scol.as<char>() + 4LL * tot[0], 4LL * (nu_alloc - tot[0]));
+    z.add(pb->sent.as<char>() + 8LL * tot[1], 8LL * (nl_alloc - tot[1]));
+    zero_many(z, s);
+  }
   launch_sell_fill(N, nslices, row_ptr, pb->col.as<int>(), pb->vals.as<double>(), pb->Linv.as<double>(), lptr,
                    pb->lsrc.as<int>(), sbu, sbl, pb->sblk.as<float>(), bf16 ? pb->sblk16.as<uint32_t>() : nullptr,
                    pb->scol.as<int>(),
@@ -608,8 +641,11 @@ bf_status size_constraint_buffers(bf_problem* pb, int n_pt, int n_ee) {
   ALLOC(c, pb->r, 12LL * N4 * two);
   ALLOC(c, pb->pring, 12LL * N4 * kPRing);
   ALLOC(c, pb->q, 12LL * N4 * two);
-  for (DevBuf* b : {&pb->Lf, &pb->Linv, &pb->bhat, &pb->xs, &pb->rd, &pb->r, &pb->pring, &pb->q})
-    HIPCHK(c, hipMemsetAsync(b->p, 0, b->bytes, s));
+  {
+    ZeroList z;
+    for (DevBuf* b : {&pb->Lf, &pb->Linv, &pb->bhat, &pb->xs, &pb->rd, &pb->r, &pb->pring, &pb->q}) z.add(b->p, b->bytes);
+    zero_many(z, s);
+  }
   HIPCHK(c, hipStreamSynchronize(s));
   ALLOC(c, pb->part, 8LL * (pcg_fused_groups(N) ? kResidentParts : kPartsPerSystem));
   ALLOC(c, pb->pout, 24LL * N);
@@ -641,7 +677,6 @@ bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* o, double* p_out, 
   hipStream_t s = c->stream;
   const int N = pb->N, n = pb->n_c;
   int* flags = pb->flags.as<int>();
-  int* row_ptr = pb->row_ptr.as<int>();
   {
     const bf_status r0 = step_assemble(pb, bf16);
     if (r0 != BF_OK) return r0;
@@ -852,10 +887,8 @@ bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* o, double* p_out, 
   HIPCHK(c, hipMemcpyAsync(p_out, pb->pout.p, 24LL * N, kind_out(mem), s));
   const double refine_rr = pb->host_sc->rr_true, refine_bb = pb->host_sc->bb;
   HIPCHK(c, hipMemcpyAsync(pb->host_sc, S.sc, sizeof(PcgScalars), hipMemcpyDeviceToHost, s));
-  int nnzb = 0, hflags = 0;
-  HIPCHK(c, hipMemcpyAsync(&nnzb, row_ptr + N, sizeof(int), hipMemcpyDeviceToHost, s));
-  HIPCHK(c, hipMemcpyAsync(&hflags, flags, sizeof(int), hipMemcpyDeviceToHost, s));
   HIPCHK(c, hipStreamSynchronize(s));
+  const int nnzb = pb->host_sc->nnzb, hflags = pb->host_sc->aflags;
   pb->nnzb_last = nnzb;
   pb->stepped = true;
   const PcgScalars& h = *pb->host_sc;

@@ -233,12 +233,12 @@ __global__ void k_lower_count(int N, const int* __restrict__ row_ptr, const int*
 }
 
 __global__ void k_lower_fill(int N, const int* __restrict__ row_ptr, const int* __restrict__ col,
-                             const int* __restrict__ lptr, int* lcur, int* lsrc) {
+                             const int* __restrict__ lptr, int* lcnt, int* lsrc) {
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= N) return;
   for (int s = row_ptr[r] + 1; s < row_ptr[r + 1]; ++s) {
     const int c = col[s];
-    lsrc[lptr[c] + atomicAdd(&lcur[c], 1)] = r;
+    lsrc[lptr[c] + atomicSub(&lcnt[c], 1) - 1] = r;   // (sorted afterwards; the counts end at zero)
   }
 }
 
@@ -275,20 +275,78 @@ __device__ inline uint32_t bf16_rne(float f) {
 // each block twice at nearly the same time.  Shorter rows are padded: an
 // upper pad has a zero block and its own row as column; a lower pad points at
 // the zero block stored after the last upper slot.
-__global__ void k_slice_widths(int N, int nslices, const int* __restrict__ row_ptr, const int* __restrict__ lptr,
-                               int* __restrict__ cu, int* __restrict__ cl, int* __restrict__ wmax) {
-  const int sl = blockIdx.x * blockDim.x + threadIdx.x;
+// A wavefront per slice, a lane per row.
+__global__ void __launch_bounds__(kBlock)
+k_slice_widths(int N, int nslices, const int* __restrict__ row_ptr, const int* __restrict__ lptr,
+               int* __restrict__ cu, int* __restrict__ cl, int* __restrict__ wmax) {
+  const int r = blockIdx.x * kBlock + threadIdx.x, sl = r / kSlice;
   if (sl >= nslices) return;
-  int wu = 0, wl = 0;
-  const int r1 = min(N, (sl + 1) * kSlice);
-  for (int r = sl * kSlice; r < r1; ++r) {
-    wu = max(wu, row_ptr[r + 1] - row_ptr[r] - 1);
-    wl = max(wl, lptr[r + 1] - lptr[r]);
+  int wu = r < N ? row_ptr[r + 1] - row_ptr[r] - 1 : 0, wl = r < N ? lptr[r + 1] - lptr[r] : 0;
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) {
+    wu = max(wu, __shfl_xor(wu, off, kWave));
+    wl = max(wl, __shfl_xor(wl, off, kWave));
   }
+  if (r % kSlice) return;
   cu[sl] = wu * kSlice;
   cl[sl] = wl * kSlice;
-  atomicMax(&wmax[0], wu);
-  atomicMax(&wmax[1], wl);
+  if (wmax) {
+    atomicMax(&wmax[0], wu);
+    atomicMax(&wmax[1], wl);
+  }
+}
+
+// Both scans of the widths and what the host has to know of them, out[4] =
+// (upper slots, lower slots, largest upper and lower width), by one workgroup:
+// up to kOffsetSlices slices this is one short launch in the place of two scans
+// and of three copies to the host (out is pinned memory).
+__global__ void __launch_bounds__(kOffsetSlices)
+k_slice_offsets(int nslices, int* __restrict__ cu, int* __restrict__ cl, int* __restrict__ out) {
+  __shared__ int tot[4][kOffsetSlices / kWave];
+  const int t = threadIdx.x, lane = t % kWave, wv = t / kWave;
+  const int a = t < nslices ? cu[t] : 0, b = t < nslices ? cl[t] : 0;
+  int sa = a, sb = b, ma = a, mb = b;
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const int ua = __shfl_up(sa, off, kWave), ub = __shfl_up(sb, off, kWave);
+    if (lane >= off) {
+      sa += ua;
+      sb += ub;
+    }
+    ma = max(ma, __shfl_xor(ma, off, kWave));
+    mb = max(mb, __shfl_xor(mb, off, kWave));
+  }
+  if (lane == kWave - 1) {
+    tot[0][wv] = sa;
+    tot[1][wv] = sb;
+    tot[2][wv] = ma;
+    tot[3][wv] = mb;
+  }
+  __syncthreads();
+  int oa = 0, ob = 0, xa = 0, xb = 0, na = 0, nb = 0;
+#pragma unroll
+  for (int w = 0; w < kOffsetSlices / kWave; ++w) {
+    if (w < wv) {
+      oa += tot[0][w];
+      ob += tot[1][w];
+    }
+    na += tot[0][w];
+    nb += tot[1][w];
+    xa = max(xa, tot[2][w]);
+    xb = max(xb, tot[3][w]);
+  }
+  if (t < nslices) {
+    cu[t] = oa + sa - a;
+    cl[t] = ob + sb - b;
+  }
+  if (t == 0) {
+    cu[nslices] = na;
+    cl[nslices] = nb;
+    out[0] = na;
+    out[1] = nb;
+    out[2] = xa / kSlice;
+    out[3] = xb / kSlice;
+  }
 }
 
 // Upper slots: H_hat_rc = M_r H_rc M_c^T (M = L^{-1}) for every upper
@@ -400,8 +458,12 @@ void launch_lower_fill(int N, const int* row_ptr, const int* col, const int* lpt
 
 void launch_slice_widths(int N, int nslices, const int* row_ptr, const int* lptr, int* cu, int* cl, int* wmax,
                          hipStream_t s) {
-  hipLaunchKernelGGL(k_slice_widths, dim3(div_up(nslices, kBlock)), dim3(kBlock), 0, s, N, nslices, row_ptr, lptr, cu,
-                     cl, wmax);
+  hipLaunchKernelGGL(k_slice_widths, dim3(div_up((long long)nslices * kSlice, kBlock)), dim3(kBlock), 0, s, N, nslices,
+                     row_ptr, lptr, cu, cl, wmax);
+}
+
+void launch_slice_offsets(int nslices, int* cu, int* cl, int* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_slice_offsets, dim3(1), dim3(kOffsetSlices), 0, s, nslices, cu, cl, out);
 }
 
 void launch_sell_fill(int N, int nslices, const int* row_ptr, const int* col, const double* vals, const double* Linv,

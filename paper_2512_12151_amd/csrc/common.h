@@ -69,6 +69,7 @@ struct PcgScalars {
   double tol2;       // tol^2
   double stat_pinf;  // max |p_i| of the result
   double stat_viol;  // max_i max(0, -c_i)
+  int aflags, nnzb;  // the assembly's error flags and block count, at the end of the solve
   double rt_ref;     // |L r|^2 right after the last residual replacement (or |b|^2)
   float alpha_hist[8];   // alpha_j at j % kXBatch (written by workgroup 0 of the update kernel)
   PcgCtl ctl[2];         // state of a one-kernel solve (pcg_fused.hip), by the parity of the launch
@@ -141,6 +142,7 @@ struct PcgSystem {
   int fused_wg0, fused_nwg;
   const float* bhat;
   const int* aflags;             // the assembly's error flags, or null
+  const int* nnzb;               // its block count
   unsigned long long* hstat;     // pinned host words: launches << 32 | end code, iteration of the end, PcgCtl::apart; or null
   int report_mask;               // launches with (number & mask) == 0 report, and the end does
 };
@@ -178,6 +180,19 @@ void scan_exclusive(const int* in, int* out, long long n, int* total, int* tmp, 
 // Sort every segment [ptr[i], ptr[i+1]) of keys ascending (a wavefront per segment; stable).
 void sort_segments(int* keys, const int* ptr, int nseg, hipStream_t s);
 void fill_int(int* a, int v, long long n, hipStream_t s);
+// Several arrays of 4-byte words zeroed in one launch.
+struct ZeroList {
+  static constexpr int kMax = 8;
+  int n = 0;
+  int* p[kMax];
+  long long words[kMax];
+  void add(void* a, long long bytes) {   // (no more than kMax)
+    if (bytes < 4) return;
+    p[n] = static_cast<int*>(a);
+    words[n++] = bytes / 4;
+  }
+};
+void zero_many(const ZeroList& z, hipStream_t s);
 
 // setup.hip: per-mesh work
 void launch_check_tets(const int4* tets, int T, int N, int* flags, hipStream_t s);
@@ -343,6 +358,10 @@ void launch_assemble_rows(int N, long long cap, const int* row_ptr, const int* c
 void launch_lower_count(int N, const int* row_ptr, const int* col, int* lcnt, hipStream_t s);
 void launch_lower_fill(int N, const int* row_ptr, const int* col, const int* lptr, int* lcur, int* lsrc,
                        hipStream_t s);
+// Scans both widths in place (at most kOffsetSlices slices); out, pinned: the
+// slots, upper and lower, and the largest widths.
+constexpr int kOffsetSlices = 1024;
+void launch_slice_offsets(int nslices, int* cu, int* cl, int* out, hipStream_t s);
 void launch_slice_widths(int N, int nslices, const int* row_ptr, const int* lptr, int* cu, int* cl, int* wmax,
                          hipStream_t s);
 // The SpMV visits upper and lower slots in pairs, kPairs per step, and reads

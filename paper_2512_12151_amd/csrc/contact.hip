@@ -178,14 +178,14 @@ __global__ void k_inc_count(const int4* __restrict__ ids, int n_c, int* cnt) {
   atomicAdd(&cnt[t.x], 1); atomicAdd(&cnt[t.y], 1); atomicAdd(&cnt[t.z], 1); atomicAdd(&cnt[t.w], 1);
 }
 
-__global__ void k_inc_fill(const int4* __restrict__ ids, int n_c, const int* __restrict__ ptr, int* cursor,
+__global__ void k_inc_fill(const int4* __restrict__ ids, int n_c, const int* __restrict__ ptr, int* cnt,
                            int* inc) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n_c) return;
   const int4 t = ids[i];
   for (int a = 0; a < 4; ++a) {
     const int v = vtx(t, a);
-    inc[ptr[v] + atomicAdd(&cursor[v], 1)] = 4 * i + a;
+    inc[ptr[v] + atomicSub(&cnt[v], 1) - 1] = 4 * i + a;   // (sorted afterwards; the counts end at zero)
   }
 }
 
@@ -498,9 +498,9 @@ void launch_vertex_incidence_count(const int4* ids, int n_c, int* cnt, hipStream
   if (n_c > 0) hipLaunchKernelGGL(k_inc_count, dim3(div_up(n_c, kBlock)), dim3(kBlock), 0, s, ids, n_c, cnt);
 }
 
-void launch_vertex_incidence_fill(const int4* ids, int n_c, const int* ptr, int* cursor, int* inc, hipStream_t s) {
+void launch_vertex_incidence_fill(const int4* ids, int n_c, const int* ptr, int* cnt, int* inc, hipStream_t s) {
   if (n_c > 0)
-    hipLaunchKernelGGL(k_inc_fill, dim3(div_up(n_c, kBlock)), dim3(kBlock), 0, s, ids, n_c, ptr, cursor, inc);
+    hipLaunchKernelGGL(k_inc_fill, dim3(div_up(n_c, kBlock)), dim3(kBlock), 0, s, ids, n_c, ptr, cnt, inc);
 }
 
 void launch_candidate_count(const int* erow_ptr, const int* vptr, const int* vinc, const int4* ids, int N,

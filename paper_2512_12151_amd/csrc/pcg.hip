@@ -916,7 +916,7 @@ __global__ void __launch_bounds__(kBlock) k_sum_to(const double* __restrict__ pa
 
 __global__ void __launch_bounds__(kBlock)
 k_finish_scalars(const double* __restrict__ part, int n, const double* __restrict__ viol_part, int nviol,
-                 PcgScalars* sc) {
+                 PcgScalars* sc, const int* __restrict__ aflags, const int* __restrict__ nnzb) {
   double m = 0.0, vm = 0.0;
   for (int k = threadIdx.x; k < n; k += kBlock) m = fmax(m, part[k]);
   for (int k = threadIdx.x; k < nviol; k += kBlock) vm = fmax(vm, viol_part[k]);
@@ -925,6 +925,8 @@ k_finish_scalars(const double* __restrict__ part, int n, const double* __restric
   if (threadIdx.x == 0) {
     sc->stat_pinf = m;
     sc->stat_viol = vm;
+    sc->aflags = *aflags;   // with these the host needs one copy
+    sc->nnzb = *nnzb;
   }
 }
 
@@ -1007,7 +1009,8 @@ void launch_pcg_finish(const PcgSystem& S, const double* Linv, double* pout, con
   double* part = S.part + kPartPQ;
   hipLaunchKernelGGL(k_finish<double>, dim3(g), dim3(kVecBlock), 0, s, S.N, S.N4, Linv, (const double*)S.x, pout,
                      part);
-  hipLaunchKernelGGL(k_finish_scalars, dim3(1), dim3(kBlock), 0, s, (const double*)part, g, viol_part, nviol, S.sc);
+  hipLaunchKernelGGL(k_finish_scalars, dim3(1), dim3(kBlock), 0, s, (const double*)part, g, viol_part, nviol, S.sc,
+                     S.aflags, S.nnzb);
 }
 
 void launch_pcg_init_from64(const PcgSystem& S, const double* rd, const double* rpart, int nparts, double tol,
@@ -1060,7 +1063,8 @@ void launch_pcg_finish64(const PcgSystem& S, const double* Linv, const double* x
   const int g = pcg_vec_groups(S.N);
   double* part = S.part + kPartPQ;
   hipLaunchKernelGGL(k_finish<double>, dim3(g), dim3(kVecBlock), 0, s, S.N, S.N4, Linv, xd, pout, part);
-  hipLaunchKernelGGL(k_finish_scalars, dim3(1), dim3(kBlock), 0, s, (const double*)part, g, viol_part, nviol, S.sc);
+  hipLaunchKernelGGL(k_finish_scalars, dim3(1), dim3(kBlock), 0, s, (const double*)part, g, viol_part, nviol, S.sc,
+                     S.aflags, S.nnzb);
 }
 
 }  // namespace bfal

@@ -57,6 +57,7 @@ struct bf_problem {
   long long cap_nnzb = 0, cap_cand = 0;
   long long nslot_u = 0, nslot_l = 0;   // slots of the sliced storage of the last step
   PcgScalars* host_sc = nullptr;
+  int* host_slots = nullptr;                 // pinned: slots and widths of the step's sliced storage
   unsigned long long* host_stat = nullptr;   // pinned: a one-kernel solve's report (PcgSystem::hstat)
   // collision queries: the surface (built at the first call), two BVHs, the
   // colliding pairs and the active-set rebuild
@@ -123,6 +124,13 @@ inline bf_status flags_to_status(bf_context* c, int flags) {
   return BF_OK;
 }
 
+// Workgroups of the one-kernel iteration, 0 where the two kernels take the system
+// (its loads use 32-bit byte offsets: the upper blocks are its largest array).
+inline int fused_groups(const bf_problem* pb) {
+  const long long slots = pb->nslot_u + 2 * kSlice;
+  return 36 * slots < (1LL << 32) ? pcg_fused_groups(pb->N) : 0;
+}
+
 // The PCG system of a problem's current step (its buffers, grids and row ranges).
 inline PcgSystem system_of(bf_problem* pb) {
   PcgSystem S;
@@ -149,11 +157,10 @@ inline PcgSystem system_of(bf_problem* pb) {
   S.vec_wg0 = 0;
   S.vec_nwg = pcg_vec_groups(pb->N);
   S.fused_wg0 = 0;
-  // (its loads use 32-bit byte offsets: the upper blocks are its largest array)
-  const long long slots = pb->nslot_u + 2 * kSlice;
-  S.fused_nwg = 36 * slots < (1LL << 32) ? pcg_fused_groups(pb->N) : 0;
+  S.fused_nwg = fused_groups(pb);
   S.bhat = pb->bhat.as<float>();
   S.aflags = pb->flags.as<int>();
+  S.nnzb = pb->row_ptr.as<int>() + pb->N;
   S.hstat = nullptr;
   S.report_mask = 3;
   return S;

@@ -174,3 +174,18 @@ def test_solves_side_by_side_equal_the_same_solves_alone():
         t.join(100)
         assert not t.is_alive()
     assert not bad
+
+
+STORAGE = [
+    ("1024 rows", (7, 7, 15)),      # one tile of the scans
+    ("1025 rows", (4, 4, 40)),      # two tiles
+    ("1024 slices", (15, 63, 63)),  # 65,536 rows: the most slices whose offsets one workgroup scans
+    ("1040 slices", (15, 63, 64)),
+]
+
+
+@pytest.mark.parametrize("name,cells", STORAGE, ids=[c[0] for c in STORAGE])
+def test_sliced_storage_at_the_edges_of_its_scans(name, cells):
+    """The solution against the assembled matrix, which is read from the row
+    storage: a wrong slot offset would leave a block out of the product."""
+    test_solution_of_the_assembled_system(name, lambda: _box(*cells), 1)
