@@ -88,29 +88,33 @@ bf_status ensure_sort_tmp(bf_problem* pb, int n) {
   return BF_OK;
 }
 
-// A BVH over n primitives of k vertices (ids AoS [n][k]).
-bf_status build_tree(bf_problem* pb, int n, const int* ids, int k, const double* xh, DevBuf& box, DevBuf& key,
-                     DevBuf& key2, DevBuf& child, DevBuf& parent, DevBuf& node, DevBuf& arrive) {
-  // parent holds the internal nodes' leaf ranges, arrive the sparse table of run boxes
+// The buffers of a BVH over n primitives of k vertices (ids AoS [n][k]); part
+// holds both trees' partial bounds.
+bf_status size_tree(bf_problem* pb, int n, const int* ids, int k, void* part, DevBuf& box, DevBuf& key, DevBuf& key2,
+                    DevBuf& child, DevBuf& range, DevBuf& node, DevBuf& table, TreeSide* out) {
   bf_context* c = pb->ctx;
-  hipStream_t s = c->stream;
+  *out = TreeSide{};
   if (n == 0) return BF_OK;
   ALLOC(c, box, 24LL * n);
   ALLOC(c, key, 8LL * n);
   ALLOC(c, key2, 8LL * n);
   ALLOC(c, child, 8LL * std::max(n - 1, 1));
-  ALLOC(c, parent, 8LL * std::max(n - 1, 1));          // internal node leaf ranges
+  ALLOC(c, range, 8LL * std::max(n - 1, 1));
   ALLOC(c, node, ccd_node_bytes(n));
-  ALLOC(c, arrive, 24LL * n * ccd_table_levels(n));    // sparse table of run boxes
-  ALLOC(c, pb->bpart, 24LL * ccd_bounds_parts(n));
-  launch_prim_boxes(n, ids, k, pb->x.as<double>(), xh, box.p, s);
-  launch_morton(n, box.p, pb->bpart.p, key.as<unsigned long long>(), s);
-  bf_status st = ensure_sort_tmp(pb, n);
-  if (st != BF_OK) return st;
-  HIPCHK(c, ccd_sort_keys(pb->sort_tmp.p, pb->sort_tmp.bytes, key.as<unsigned long long>(),
-                          key2.as<unsigned long long>(), n, s));
-  launch_build_tree(n, key2.as<unsigned long long>(), box.p, child.as<int2>(), parent.as<int2>(), node.p, arrive.p,
-                    s);
+  ALLOC(c, table, 24LL * n * ccd_table_levels(n));
+  *out = TreeSide{n,
+                  k,
+                  ids,
+                  box.p,
+                  part,
+                  ccd_bounds_parts(n),
+                  ccd_table_levels(n),
+                  key.as<unsigned long long>(),
+                  key2.as<unsigned long long>(),
+                  child.as<int2>(),
+                  range.as<int2>(),
+                  node.p,
+                  table.p};
   return BF_OK;
 }
 
@@ -128,12 +132,23 @@ bf_status collide(bf_problem* pb, const double* xh, double sep, Collide& out) {
   bf_status st = ensure_surface(pb);
   if (st != BF_OK) return st;
   HIPCHK(c, hipEventRecord(pb->ev[0], s));
-  st = build_tree(pb, pb->nF, pb->stris.as<int>(), 3, xh, pb->tbox, pb->tkey, pb->tkey2, pb->tchild, pb->tparent,
-                  pb->tnode, pb->tarrive);
+  const int pf = ccd_bounds_parts(pb->nF);
+  ALLOC(c, pb->bpart, 24LL * (pf + ccd_bounds_parts(pb->nE)) + 24);
+  TreeSide side_f, side_e;
+  st = size_tree(pb, pb->nF, pb->stris.as<int>(), 3, pb->bpart.p, pb->tbox, pb->tkey, pb->tkey2, pb->tchild,
+                 pb->tparent, pb->tnode, pb->tarrive, &side_f);
   if (st != BF_OK) return st;
-  st = build_tree(pb, pb->nE, pb->sedges.as<int>(), 2, xh, pb->ebox, pb->ekey, pb->ekey2, pb->echild, pb->eparent,
-                  pb->enode, pb->earrive);
+  st = size_tree(pb, pb->nE, pb->sedges.as<int>(), 2, pb->bpart.as<char>() + 24LL * pf, pb->ebox, pb->ekey, pb->ekey2,
+                 pb->echild, pb->eparent, pb->enode, pb->earrive, &side_e);
   if (st != BF_OK) return st;
+  st = ensure_sort_tmp(pb, std::max(pb->nF, pb->nE));
+  if (st != BF_OK) return st;
+  launch_tree_keys(side_f, side_e, pb->x.as<double>(), xh, s);
+  for (const TreeSide* t : {&side_f, &side_e})
+    if (t->n)
+      HIPCHK(c, ccd_sort_keys(pb->sort_tmp.p, pb->sort_tmp.bytes, t->key, const_cast<unsigned long long*>(t->sorted),
+                              t->n, s));
+  launch_build_trees(side_f, side_e, s);
   HIPCHK(c, hipEventRecord(pb->ev[1], s));
   ALLOC(c, pb->qcount, 4 * 32);
   int* cnt = pb->qcount.as<int>();
@@ -159,8 +174,8 @@ bf_status collide(bf_problem* pb, const double* xh, double sep, Collide& out) {
       q.pairs = pb->qpairs[kind].as<int2>();
       q.toc = pb->qtoc[kind].as<double>();
       q.cap = pb->qcap[kind];
-      if (todo[kind]) fill_int(cnt + 8 * kind, 0, 8, s);
     }
+    fill_int(cnt + (todo[0] ? 0 : 8), 0, todo[0] && todo[1] ? 16 : 8, s);
     launch_queries(side[0], side[1], todo[0], todo[1], pb->x.as<double>(), xh, pb->delta, sep, cnt, s);
     int h[16];
     HIPCHK(c, hipMemcpyAsync(h, cnt, sizeof(h), hipMemcpyDeviceToHost, s));

@@ -168,56 +168,67 @@ __device__ inline void box_of(const double* x, const double* xh, const int* v, i
   }
 }
 
-// FP32 swept boxes of the primitives (k vertices each, ids AoS [n][k] in
-// stride st), rounded outward; and their centres for the Morton codes.
-__global__ void k_prim_boxes(int n, const int* __restrict__ ids, int k, int st, const double* __restrict__ x,
-                             const double* __restrict__ xh, Box* __restrict__ box) {
-  const int i = blockIdx.x * kCcdBlock + threadIdx.x;
-  if (i >= n) return;
-  int v[3];
-  for (int a = 0; a < k; ++a) v[a] = ids[(long long)st * i + a];
-  double lo[3], hi[3];
-  box_of(x, xh, v, k, lo, hi);
-  Box b;
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    b.lo[c] = __double2float_rd(lo[c]);
-    b.hi[c] = __double2float_ru(hi[c]);
-  }
-  box[i] = b;
+// The trees of a query (triangles and edges) are built side by side: a launch's
+// first workgroups take the one, the others the other.  A build is a chain of
+// launches of a few microseconds each whatever the tree's size, so two chains
+// in one cost what one does (12k edges: two chains 230 us and their gaps).
+struct Trees {
+  TreeSide side[2];
+  int groups0;   // workgroups of side 0
+};
+__device__ __forceinline__ const TreeSide& tree_of(const Trees& t, int& block) {
+  const bool first = (int)blockIdx.x < t.groups0;
+  block = first ? blockIdx.x : blockIdx.x - t.groups0;
+  return t.side[first ? 0 : 1];
 }
 
-// Bounds of all leaf boxes: per-workgroup partial boxes, then one workgroup
-// combines them.
-__global__ void k_bounds_part(int n, const Box* __restrict__ box, Box* __restrict__ part) {
-  __shared__ float red[6][kCcdBlock];
+// FP32 swept boxes of the primitives (k vertices each, ids AoS [n][k]), rounded
+// outward, and per workgroup the bounds of its boxes.
+__global__ void __launch_bounds__(kCcdBlock)
+k_prim_boxes(Trees trees, const double* __restrict__ x, const double* __restrict__ xh) {
+  int block;
+  const TreeSide& T = tree_of(trees, block);
+  Box* __restrict__ box = static_cast<Box*>(T.box);
+  __shared__ float red[6][kCcdBlock / kWave];
   float b[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
-  for (int i = blockIdx.x * kCcdBlock + threadIdx.x; i < n; i += gridDim.x * kCcdBlock) {
+  for (int i = block * kCcdBlock + threadIdx.x; i < T.n; i += T.nparts * kCcdBlock) {
+    int v[3];
+    for (int a = 0; a < T.k; ++a) v[a] = T.ids[(long long)T.k * i + a];
+    double lo[3], hi[3];
+    box_of(x, xh, v, T.k, lo, hi);
+    Box o;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      b[c] = fminf(b[c], box[i].lo[c]);
-      b[3 + c] = fmaxf(b[3 + c], box[i].hi[c]);
+      o.lo[c] = __double2float_rd(lo[c]);
+      o.hi[c] = __double2float_ru(hi[c]);
+      b[c] = fminf(b[c], o.lo[c]);
+      b[3 + c] = fmaxf(b[3 + c], o.hi[c]);
     }
+    box[i] = o;
   }
 #pragma unroll
-  for (int c = 0; c < 6; ++c) red[c][threadIdx.x] = b[c];
+  for (int c = 0; c < 6; ++c) {
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+      const float o = __shfl_xor(b[c], off, kWave);
+      b[c] = c < 3 ? fminf(b[c], o) : fmaxf(b[c], o);
+    }
+    if (threadIdx.x % kWave == 0) red[c][threadIdx.x / kWave] = b[c];
+  }
   __syncthreads();
-  for (int off = kCcdBlock / 2; off > 0; off >>= 1) {
-    if (threadIdx.x < off)
-#pragma unroll
-      for (int c = 0; c < 6; ++c)
-        red[c][threadIdx.x] = c < 3 ? fminf(red[c][threadIdx.x], red[c][threadIdx.x + off])
-                                    : fmaxf(red[c][threadIdx.x], red[c][threadIdx.x + off]);
-    __syncthreads();
-  }
   if (threadIdx.x == 0) {
     Box o;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       o.lo[c] = red[c][0];
       o.hi[c] = red[3 + c][0];
+#pragma unroll
+      for (int w = 1; w < kCcdBlock / kWave; ++w) {
+        o.lo[c] = fminf(o.lo[c], red[c][w]);
+        o.hi[c] = fmaxf(o.hi[c], red[3 + c][w]);
+      }
     }
-    part[blockIdx.x] = o;
+    static_cast<Box*>(T.part)[block] = o;
   }
 }
 
@@ -232,16 +243,21 @@ __device__ inline unsigned int spread10(unsigned int v) {
 
 // 64-bit sort keys: the 30-bit Morton code of the box centre (in the scene
 // bounds) above the primitive index, so equal codes order by index.
-__global__ void k_morton(int n, const Box* __restrict__ box, const Box* __restrict__ part, int nparts,
-                         unsigned long long* __restrict__ key) {
-  // the scene's bounds from the partial boxes, one per thread (nparts <= kCcdBlock)
+__global__ void __launch_bounds__(kCcdBlock) k_morton(Trees trees) {
+  int block;
+  const TreeSide& T = tree_of(trees, block);
+  const int n = T.n, nparts = T.nparts;
+  const Box* __restrict__ box = static_cast<const Box*>(T.box);
+  const Box* __restrict__ part = static_cast<const Box*>(T.part);
+  unsigned long long* __restrict__ key = T.key;
+  // the scene's bounds from the partial boxes
   __shared__ float red[6][kCcdBlock / kWave];
   float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  if ((int)threadIdx.x < nparts)
+  for (int p = threadIdx.x; p < nparts; p += kCcdBlock)
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      lo[c] = part[threadIdx.x].lo[c];
-      hi[c] = part[threadIdx.x].hi[c];
+      lo[c] = fminf(lo[c], part[p].lo[c]);
+      hi[c] = fmaxf(hi[c], part[p].hi[c]);
     }
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
@@ -263,7 +279,7 @@ __global__ void k_morton(int n, const Box* __restrict__ box, const Box* __restri
       lo[c] = fminf(lo[c], red[c][w]);
       hi[c] = fmaxf(hi[c], red[3 + c][w]);
     }
-  const int i = blockIdx.x * kCcdBlock + threadIdx.x;
+  const int i = block * kCcdBlock + threadIdx.x;
   if (i >= n) return;
   unsigned int code = 0;
 #pragma unroll
@@ -288,10 +304,15 @@ __device__ inline int common_prefix(const unsigned long long* key, int n, int i,
 // nodes or leaves (leaf k is node n - 1 + k).
 // The same launch writes level 0 of the table of node boxes: the primitive
 // boxes in key order.
-__global__ void k_karras(int n, const unsigned long long* __restrict__ key, const Box* __restrict__ pbox,
-                         int2* __restrict__ child, int2* __restrict__ range, Box* __restrict__ level0) {
-  const int i = blockIdx.x * kCcdBlock + threadIdx.x;
-  if (i < n) level0[i] = pbox[(int)(key[i] & 0xffffffffu)];
+__global__ void __launch_bounds__(kCcdBlock) k_karras(Trees trees) {
+  int block;
+  const TreeSide& T = tree_of(trees, block);
+  const int n = T.n;
+  const unsigned long long* __restrict__ key = T.sorted;
+  int2* __restrict__ child = T.child;
+  int2* __restrict__ range = T.range;
+  const int i = block * kCcdBlock + threadIdx.x;
+  if (i < n) static_cast<Box*>(T.table)[i] = static_cast<const Box*>(T.box)[(int)(key[i] & 0xffffffffu)];
   if (i >= n - 1) return;
   const int d = common_prefix(key, n, i, i + 1) - common_prefix(key, n, i, i - 1) >= 0 ? 1 : -1;
   const int dmin = common_prefix(key, n, i, i - d);
@@ -336,8 +357,13 @@ __device__ inline Box box_union(const Box& a, const Box& b) {
 // leaves 30 -> 11 us, of 40k leaves 37 -> 17, gaps between launches not counted).
 constexpr int kTableStep = 4;
 __global__ void __launch_bounds__(kCcdBlock)
-k_sparse_levels(int n, int h, int levels, const Box* __restrict__ prev, Box* __restrict__ next) {
-  const int i = blockIdx.x * kCcdBlock + threadIdx.x;
+k_sparse_levels(Trees trees, int k) {
+  int block;
+  const TreeSide& T = tree_of(trees, block);
+  const int n = T.n, h = 1 << (k - 1), levels = T.levels - k;
+  const Box* __restrict__ prev = static_cast<const Box*>(T.table) + (long long)(k - 1) * n;
+  Box* __restrict__ next = static_cast<Box*>(T.table) + (long long)k * n;
+  const int i = block * kCcdBlock + threadIdx.x;
   if (i + 2LL * h > n) return;
   Box b[1 << kTableStep];
 #pragma unroll
@@ -367,9 +393,15 @@ __device__ inline Box box_of_node(int v, int n, const int2* __restrict__ range, 
   return box_union(lv[r.x], lv[r.y - (1 << m) + 1]);
 }
 
-__global__ void k_nodes(int n, const int2* __restrict__ child, const int2* __restrict__ range,
-                        const Box* __restrict__ table, Node* __restrict__ node) {
-  const int i = blockIdx.x * kCcdBlock + threadIdx.x;
+__global__ void __launch_bounds__(kCcdBlock) k_nodes(Trees trees) {
+  int block;
+  const TreeSide& T = tree_of(trees, block);
+  const int n = T.n;
+  const int2* __restrict__ child = T.child;
+  const int2* __restrict__ range = T.range;
+  const Box* __restrict__ table = static_cast<const Box*>(T.table);
+  Node* __restrict__ node = static_cast<Node*>(T.node);
+  const int i = block * kCcdBlock + threadIdx.x;
   if (i >= n - 1) return;
   Node o;
   o.child = child[i];
@@ -595,12 +627,22 @@ __device__ __forceinline__ void narrow(const QuerySide& q, int2 pr, const double
 }
 
 template <bool kEE>
-__global__ void __launch_bounds__(kNarrowBlock)
-k_narrow(QuerySide q, const double* __restrict__ x, const double* __restrict__ xh, double s, int* __restrict__ count) {
+__device__ __forceinline__ void narrow_all(const QuerySide& q, int block, int blocks, const double* __restrict__ x,
+                                           const double* __restrict__ xh, double s, int* __restrict__ count) {
   const long long total = *reinterpret_cast<const unsigned long long*>(count + 2);
   const long long n = total < q.cand_cap ? total : q.cand_cap;
-  for (long long k = (long long)blockIdx.x * kNarrowBlock + threadIdx.x; k < n; k += (long long)gridDim.x * kNarrowBlock)
+  for (long long k = (long long)block * kNarrowBlock + threadIdx.x; k < n; k += (long long)blocks * kNarrowBlock)
     narrow<kEE>(q, q.cand[k], x, xh, s, count);
+}
+
+__global__ void __launch_bounds__(kNarrowBlock)
+k_narrow(QuerySide pt, QuerySide ee, int pt_groups, const double* __restrict__ x, const double* __restrict__ xh,
+         double s, int* __restrict__ count) {
+  const int b = blockIdx.x;
+  if (b < pt_groups)
+    narrow_all<false>(pt, b, pt_groups, x, xh, s, count);
+  else
+    narrow_all<true>(ee, b - pt_groups, gridDim.x - pt_groups, x, xh, s, count + 8);
 }
 
 // Canonical 64-bit order of a colliding pair: query index above tree index
@@ -875,34 +917,24 @@ hipError_t ccd_sort_pairs(void* tmp, size_t tmp_bytes, const unsigned long long*
   return hipcub::DeviceRadixSort::SortPairs(tmp, tmp_bytes, kin, kout, vin, vout, n, 0, 64, s);
 }
 
+// The keys' order is that of their 30-bit codes: equal codes keep the order they
+// come in, which is that of the indices below them (the sort is stable).
+constexpr int kKeyBit0 = 32, kKeyBit1 = 62;
+
 size_t ccd_sort_keys_tmp_bytes(int n) {
   size_t bytes = 0;
-  (void)hipcub::DeviceRadixSort::SortKeys(nullptr, bytes, (unsigned long long*)nullptr, (unsigned long long*)nullptr, n, 0,
-                                    64, (hipStream_t)0);
+  (void)hipcub::DeviceRadixSort::SortKeys(nullptr, bytes, (unsigned long long*)nullptr, (unsigned long long*)nullptr, n,
+                                          kKeyBit0, kKeyBit1, (hipStream_t)0);
   return bytes;
 }
 
 hipError_t ccd_sort_keys(void* tmp, size_t tmp_bytes, const unsigned long long* kin, unsigned long long* kout, int n,
                          hipStream_t s) {
-  return hipcub::DeviceRadixSort::SortKeys(tmp, tmp_bytes, kin, kout, n, 0, 64, s);
+  return hipcub::DeviceRadixSort::SortKeys(tmp, tmp_bytes, kin, kout, n, kKeyBit0, kKeyBit1, s);
 }
 
-void launch_prim_boxes(int n, const int* ids, int k, const double* x, const double* xh, void* box, hipStream_t s) {
-  if (n > 0)
-    hipLaunchKernelGGL(k_prim_boxes, dim3(div_up(n, kCcdBlock)), dim3(kCcdBlock), 0, s, n, ids, k, k, x, xh,
-                       static_cast<Box*>(box));
-}
-
-int ccd_bounds_parts(int n) { return std::min(div_up(n, kCcdBlock), 256); }
-
-void launch_morton(int n, const void* box, void* part, unsigned long long* key, hipStream_t s) {
-  if (n <= 0) return;
-  const int np = ccd_bounds_parts(n);
-  hipLaunchKernelGGL(k_bounds_part, dim3(np), dim3(kCcdBlock), 0, s, n, static_cast<const Box*>(box),
-                     static_cast<Box*>(part));
-  hipLaunchKernelGGL(k_morton, dim3(div_up(n, kCcdBlock)), dim3(kCcdBlock), 0, s, n, static_cast<const Box*>(box),
-                     static_cast<const Box*>(part), np, key);
-}
+// (four workgroups per compute unit, and no more partial boxes than k_morton reads at once in a few loads)
+int ccd_bounds_parts(int n) { return std::min(div_up(n, kCcdBlock), 1024); }
 
 int ccd_table_levels(int n) {
   int L = 1;
@@ -910,21 +942,35 @@ int ccd_table_levels(int n) {
   return L;
 }
 
-void launch_build_tree(int n, const unsigned long long* key, const void* pbox, int2* child, int2* range, void* node,
-                       void* table, hipStream_t s) {
-  if (n <= 0) return;
-  Box* T = static_cast<Box*>(table);
-  hipLaunchKernelGGL(k_karras, dim3(div_up(n, kCcdBlock)), dim3(kCcdBlock), 0, s, n, key,
-                     static_cast<const Box*>(pbox), child, range, T);
-  if (n == 1) return;
-  const int L = ccd_table_levels(n);
-  for (int k = 1; k < L; k += kTableStep) {
-    const int h = 1 << (k - 1);
-    hipLaunchKernelGGL(k_sparse_levels, dim3(div_up(n - 2 * h + 1, kCcdBlock)), dim3(kCcdBlock), 0, s, n, h, L - k,
-                       T + (long long)(k - 1) * n, T + (long long)k * n);
+namespace {
+// Workgroups of both sides for as many threads each.
+unsigned split(Trees& t, long long n0, long long n1) {
+  t.groups0 = div_up(std::max(n0, 0LL), kCcdBlock);
+  return (unsigned)(t.groups0 + div_up(std::max(n1, 0LL), kCcdBlock));
+}
+}  // namespace
+
+void launch_tree_keys(const TreeSide& a, const TreeSide& b, const double* x, const double* xh, hipStream_t s) {
+  Trees t{{a, b}, a.n > 0 ? a.nparts : 0};
+  const unsigned g = t.groups0 + (b.n > 0 ? b.nparts : 0);
+  if (!g) return;
+  hipLaunchKernelGGL(k_prim_boxes, dim3(g), dim3(kCcdBlock), 0, s, t, x, xh);
+  const unsigned gm = split(t, a.n, b.n);
+  hipLaunchKernelGGL(k_morton, dim3(gm), dim3(kCcdBlock), 0, s, t);
+}
+
+void launch_build_trees(const TreeSide& a, const TreeSide& b, hipStream_t s) {
+  Trees t{{a, b}, 0};
+  unsigned g = split(t, a.n, b.n);
+  if (!g) return;
+  hipLaunchKernelGGL(k_karras, dim3(g), dim3(kCcdBlock), 0, s, t);
+  for (int k = 1; k < std::max(a.levels, b.levels); k += kTableStep) {
+    const long long h2 = 2LL << (k - 1);
+    g = split(t, a.n - h2 + 1, b.n - h2 + 1);
+    if (g) hipLaunchKernelGGL(k_sparse_levels, dim3(g), dim3(kCcdBlock), 0, s, t, k);
   }
-  hipLaunchKernelGGL(k_nodes, dim3(div_up(n - 1, kCcdBlock)), dim3(kCcdBlock), 0, s, n, (const int2*)child,
-                     (const int2*)range, (const Box*)T, static_cast<Node*>(node));
+  g = split(t, a.n - 1, b.n - 1);
+  if (g) hipLaunchKernelGGL(k_nodes, dim3(g), dim3(kCcdBlock), 0, s, t);
 }
 
 size_t ccd_node_bytes(int n) { return sizeof(Node) * std::max(n - 1, 1); }
@@ -934,12 +980,9 @@ void launch_queries(const QuerySide& pt, const QuerySide& ee, bool do_pt, bool d
   const int gp = do_pt ? div_up(pt.nq, kTraverseBlock) : 0, ge = do_ee ? div_up(ee.nq, kTraverseBlock) : 0;
   if (gp + ge)
     hipLaunchKernelGGL(k_traverse, dim3(gp + ge), dim3(kTraverseBlock), 0, s, pt, ee, gp, x, xh, delta, count);
-  // 16 wavefronts per compute unit: the lists are walked with a stride
-  const int grid = 256 * 16;
-  if (gp)
-    hipLaunchKernelGGL(k_narrow<false>, dim3(grid), dim3(kNarrowBlock), 0, s, pt, x, xh, sep, count);
-  if (ge)
-    hipLaunchKernelGGL(k_narrow<true>, dim3(grid), dim3(kNarrowBlock), 0, s, ee, x, xh, sep, count + 8);
+  // 16 wavefronts per compute unit and list: the lists are walked with a stride
+  const int np = gp ? 256 * 16 : 0, ne = ge ? 256 * 16 : 0;
+  if (np + ne) hipLaunchKernelGGL(k_narrow, dim3(np + ne), dim3(kNarrowBlock), 0, s, pt, ee, np, x, xh, sep, count);
 }
 
 void launch_pair_keys(int n, const int2* pairs, unsigned long long* key, int* idx, hipStream_t s) {

@@ -261,12 +261,28 @@ hipError_t ccd_sort_pairs(void* tmp, size_t tmp_bytes, const unsigned long long*
 size_t ccd_sort_keys_tmp_bytes(int n);
 hipError_t ccd_sort_keys(void* tmp, size_t tmp_bytes, const unsigned long long* kin, unsigned long long* kout, int n,
                          hipStream_t s);
-void launch_prim_boxes(int n, const int* ids, int k, const double* x, const double* xh, void* box, hipStream_t s);
 int ccd_bounds_parts(int n);
-void launch_morton(int n, const void* box, void* part, unsigned long long* key, hipStream_t s);
 int ccd_table_levels(int n);
-void launch_build_tree(int n, const unsigned long long* key, const void* pbox, int2* child, int2* range, void* node,
-                       void* table, hipStream_t s);
+// A tree over n primitives of k vertices (ids AoS [n][k]): its boxes and their
+// partial bounds, keys (before and after the sort), nodes and the table of node
+// boxes.
+struct TreeSide {
+  int n, k;
+  const int* ids;
+  void* box;
+  void* part;
+  int nparts;   // ccd_bounds_parts(n)
+  int levels;   // ccd_table_levels(n)
+  unsigned long long* key;
+  const unsigned long long* sorted;
+  int2* child;
+  int2* range;
+  void* node;
+  void* table;
+};
+// Both trees: boxes and keys, then (the keys sorted in between) the nodes.
+void launch_tree_keys(const TreeSide& a, const TreeSide& b, const double* x, const double* xh, hipStream_t s);
+void launch_build_trees(const TreeSide& a, const TreeSide& b, hipStream_t s);
 size_t ccd_node_bytes(int n);   // node storage of a tree over n primitives
 // One kind of query: its primitives, the tree they meet, the candidate list
 // (pairs within delta: query index, tree index) and the colliding pairs.
