@@ -170,9 +170,10 @@ bf_status problem_init(bf_context* c, bf_problem* pb, const bf_mesh_desc* m, int
     if (!e) HIPCHK(c, hipEventCreate(&e));
   if (!pb->host_sc) {
     static_assert(sizeof(PcgScalars) % sizeof(unsigned long long) == 0, "host_stat follows the scalars");
-    HIPCHK(c, hipHostMalloc((void**)&pb->host_sc, sizeof(PcgScalars) + 5 * sizeof(unsigned long long), hipHostMallocDefault));
+    HIPCHK(c, hipHostMalloc((void**)&pb->host_sc, sizeof(PcgScalars) + 13 * sizeof(unsigned long long), hipHostMallocDefault));
     pb->host_stat = reinterpret_cast<unsigned long long*>(pb->host_sc + 1);
     pb->host_slots = reinterpret_cast<int*>(pb->host_stat + 3);
+    pb->host_sums = reinterpret_cast<double*>(pb->host_stat + 5);
   }
   ALLOC(c, pb->scal, sizeof(PcgScalars));
   HIPCHK(c, hipMemsetAsync(pb->scal.p, 0, sizeof(PcgScalars), s));
@@ -434,7 +435,7 @@ void bf_problem_destroy(bf_problem* pb) {
                     &pb->Linv, &pb->bhat, &pb->bb_part, &pb->lcnt, &pb->lptr, &pb->lsrc, &pb->sbu, &pb->sbl,
                     &pb->wplan_ptr, &pb->wplan_sl,                    &pb->sblk, &pb->sblk16, &pb->scol, &pb->sent, &pb->xs, &pb->r, &pb->pring, &pb->q,
                     &pb->part, &pb->scal, &pb->pout, &pb->flags, &pb->scan_tmp, &pb->scratch_int,
-                    &pb->xd, &pb->rd, &pb->zd, &pb->fcg, &pb->rpart, &pb->lin64, &pb->pdir, &pb->xtrial,
+                    &pb->xd, &pb->rd, &pb->fcg, &pb->rpart, &pb->lin64, &pb->pdir, &pb->xtrial,
                     &pb->epart, &pb->stris, &pb->sedges, &pb->sverts, &pb->xq, &pb->tbox, &pb->tkey, &pb->tkey2,
                     &pb->tchild, &pb->tparent, &pb->tnode, &pb->tarrive, &pb->ebox, &pb->ekey, &pb->ekey2,
                     &pb->echild, &pb->eparent, &pb->enode, &pb->earrive, &pb->bpart, &pb->qcount, &pb->qcand[0], &pb->qcand[1], &pb->qpairs[0],
@@ -803,24 +804,22 @@ bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* o, double* p_out, 
     // makes z conjugate (in H_hat) to the last kFcgWindow directions, and
     // takes the exact step along it.  The outer Krylov recurrence on the FP32
     // operator recovers the modes the BF16 blocks cannot resolve.
-    constexpr int kFcgWindow = 4;
+    constexpr int kFcgWindow = Directions::kMax;
     const long long n3 = 3LL * S.N4;
     ALLOC(c, pb->xd, 8 * n3);
     ALLOC(c, pb->rd, 8 * n3);
-    ALLOC(c, pb->zd, 8 * n3);
     ALLOC(c, pb->fcg, 8 * n3 * 2 * kFcgWindow);
     ALLOC(c, pb->rpart, 8LL * (kMaxSpmvParts + 8 + 6 * 256 + 8));
     HIPCHK(c, hipMemsetAsync(pb->xd.p, 0, 8 * n3, s));
     HIPCHK(c, hipMemsetAsync(pb->rd.p, 0, 8 * n3, s));
-    HIPCHK(c, hipMemsetAsync(pb->zd.p, 0, 8 * n3, s));
     HIPCHK(c, hipMemsetAsync(pb->fcg.p, 0, 8 * n3 * 2 * kFcgWindow, s));
     double* rpart = pb->rpart.as<double>();
-    double* rsum = rpart + kMaxSpmvParts;        // [0] residual^2, [1] |b|^2
-    double* dpart = rsum + 8;                    // partials of the dot products
-    double* dots = dpart + 6 * 256;              // their sums
+    double* dpart = rpart + kMaxSpmvParts + 8;   // partials of the dot products
+    // sums that the host reads (pinned: written by the kernels that form them)
+    double* rsum = pb->host_sums;                // [0] residual^2, [1] |b|^2
+    double* dots = pb->host_sums + 2;            // dot products
     double* xd = pb->xd.as<double>();
     double* rd = pb->rd.as<double>();
-    double* zd = pb->zd.as<double>();
     auto Pv = [&](int j) { return pb->fcg.as<double>() + n3 * (2 * (j % kFcgWindow)); };
     auto Qv = [&](int j) { return pb->fcg.as<double>() + n3 * (2 * (j % kFcgWindow) + 1); };
     double pq_hist[kFcgWindow] = {0.0};
@@ -831,9 +830,8 @@ bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* o, double* p_out, 
     double bb = 0.0;
     for (int sw = 0;; ++sw) {
       launch_residual64(S, pb->bhat.as<float>(), xd, rd, rpart, rsum, s);
-      double hs[2] = {0.0, 0.0};
-      HIPCHK(c, hipMemcpyAsync(hs, rsum, sizeof(hs), hipMemcpyDeviceToHost, s));
       HIPCHK(c, hipStreamSynchronize(s));
+      const double hs[2] = {rsum[0], rsum[1]};
       bb = hs[1];
       const double rel = bb > 0.0 ? std::sqrt(hs[0] / bb) : 0.0;
       if (sw < 16) sweep_res[sw] = rel;
@@ -845,35 +843,31 @@ bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* o, double* p_out, 
       launch_pcg_init_from64(S16, rd, rpart, S.spmv_nwg, o->tol, o->max_iter, o->check_every, s);
       bf_status r0 = run_solve(S16, true);
       if (r0 != BF_OK) return r0;
-      if (pb->host_sc->iter == 0) {
-        HIPCHK(c, hipMemcpyAsync(zd, rd, 8 * n3, hipMemcpyDeviceToDevice, s));   // no progress: steepest descent
-      } else {
-        launch_pcg_flush(S16, s);
-        HIPCHK(c, hipMemcpyAsync(zd, S16.x, 8 * n3, hipMemcpyDeviceToDevice, s));
-      }
+      if (pb->host_sc->iter > 0) launch_pcg_flush(S16, s);
+      const double* z = pb->host_sc->iter > 0 ? S16.x : rd;   // no progress: steepest descent
       // p = z - sum_j (z.q_j / p_j.q_j) p_j over the window
       const int nwin = std::min(sweeps, kFcgWindow);
       double* P = Pv(sweeps);
       double* Q = Qv(sweeps);
-      HIPCHK(c, hipMemcpyAsync(P, zd, 8 * n3, hipMemcpyDeviceToDevice, s));
+      Directions dir;
       if (nwin > 0) {
         const double* qs[kFcgWindow];
         for (int j = 0; j < nwin; ++j) qs[j] = Qv(sweeps - 1 - j);
-        launch_dots64((int)n3, zd, qs, nwin, dpart, dots, s);
-        double hz[kFcgWindow];
-        HIPCHK(c, hipMemcpyAsync(hz, dots, 8 * nwin, hipMemcpyDeviceToHost, s));
+        launch_dots64((int)n3, z, qs, nwin, dpart, dots, s);
         HIPCHK(c, hipStreamSynchronize(s));
         for (int j = 0; j < nwin; ++j) {
           const double pqj = pq_hist[(sweeps - 1 - j) % kFcgWindow];
-          if (pqj > 0.0) launch_axpy_d((int)n3, -hz[j] / pqj, Pv(sweeps - 1 - j), P, s);
+          if (!(pqj > 0.0)) continue;
+          dir.a[dir.n] = -dots[j] / pqj;
+          dir.p[dir.n++] = Pv(sweeps - 1 - j);
         }
       }
+      launch_direction((int)n3, z, dir, P, s);
       launch_apply64(S, P, Q, s);
       const double* pr[2] = {rd, Q};
       launch_dots64((int)n3, P, pr, 2, dpart, dots, s);
-      double hd[2];
-      HIPCHK(c, hipMemcpyAsync(hd, dots, sizeof(hd), hipMemcpyDeviceToHost, s));
       HIPCHK(c, hipStreamSynchronize(s));
+      const double hd[2] = {dots[0], dots[1]};
       if (!(hd[1] > 0.0)) return fail(c, BF_ERR_NOT_SPD, "refinement direction with p^T H p <= 0");
       pq_hist[sweeps % kFcgWindow] = hd[1];
       launch_axpy_d((int)n3, hd[0] / hd[1], P, xd, s);

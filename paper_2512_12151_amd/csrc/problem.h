@@ -51,13 +51,14 @@ struct bf_problem {
   DevBuf cslot;                                // merged-pattern slots of each stencil's ten vertex pairs
   std::vector<int> h_sbu, h_sbl, h_wptr, h_wsl;  // host copies for planning (kept for the async upload)
   DevBuf xs, r, pring, q, part, scal, pout, flags, scan_tmp, scratch_int;
-  DevBuf xd, rd, zd, fcg, rpart;   // refinement: FP64 solution, residual, inner solution, directions, partials
+  DevBuf xd, rd, fcg, rpart;   // refinement: FP64 solution, residual, directions, partials
   DevBuf lin64;                    // FP64 linearization of the constraints, SoA [8][n]
   DevBuf pdir, xtrial, epart;      // subproblem: Newton direction, line-search trial state, partials
   long long cap_nnzb = 0, cap_cand = 0;
   long long nslot_u = 0, nslot_l = 0;   // slots of the sliced storage of the last step
   PcgScalars* host_sc = nullptr;
   int* host_slots = nullptr;                 // pinned: slots and widths of the step's sliced storage
+  double* host_sums = nullptr;               // pinned: up to 8 sums of the refinement
   unsigned long long* host_stat = nullptr;   // pinned: a one-kernel solve's report (PcgSystem::hstat)
   // collision queries: the surface (built at the first call), two BVHs, the
   // colliding pairs and the active-set rebuild
