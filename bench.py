@@ -88,7 +88,7 @@ def copy_ceiling():
 
 COUNTER_FILE = os.path.join(ROOT, "profiles", "k_spmv_large_hbm_counters.md")
 # the SpMV and update kernels, and the host rule that plans which slices each SpMV wavefront takes
-KERNEL_SOURCES = ["pcg.hip", "assemble.hip", "common.h", "host_rules.cpp"]
+KERNEL_SOURCES = ["pcg.hip", "pcg_device.h", "wave_ops.h", "assemble.hip", "common.h", "host_rules.cpp"]
 
 
 def kernel_sources_sha256():

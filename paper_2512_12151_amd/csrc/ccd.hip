@@ -171,7 +171,7 @@ __device__ inline void box_of(const double* x, const double* xh, const int* v, i
 // The trees of a query (triangles and edges) are built side by side: a launch's
 // first workgroups take the one, the others the other.  A build is a chain of
 // launches of a few microseconds each whatever the tree's size, so two chains
-// in one cost what one does (12k edges: two chains 230 us and their gaps).
+// in one cost what one does (2k leaves: 125 us a chain with the gaps).
 struct Trees {
   TreeSide side[2];
   int groups0;   // workgroups of side 0
@@ -353,8 +353,8 @@ __device__ inline Box box_union(const Box& a, const Box& b) {
 // entries span h = 2^(k-1) leaves: entry i of level k + j spans 2^(j+1) of them
 // and is there if i + 2^(j+1) h <= n.  A level alone is a few microseconds of
 // launch for a few hundred nanoseconds of work: four in one launch read twice
-// the boxes, out of the cache, and wait once (the levels of a tree of 12k
-// leaves 30 -> 11 us, of 40k leaves 37 -> 17, gaps between launches not counted).
+// the boxes, out of the cache, and wait once (the levels of a tree of 2k
+// leaves 23 -> 11 us, of 44k to 66k 37 -> 17, gaps between launches not counted).
 constexpr int kTableStep = 4;
 __global__ void __launch_bounds__(kCcdBlock)
 k_sparse_levels(Trees trees, int k) {

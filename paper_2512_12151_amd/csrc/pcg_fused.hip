@@ -58,7 +58,7 @@ constexpr int kRecPerLane = kFusedMaxSlices / kWave;             // partials per
 static_assert(kFusedMaxSlices % kWave == 0 && kRow3 == 3 * kWave, "wavefronts 0-2 own the entries, 3 the norms");
 
 // Loads at a 32-bit byte offset from a uniform base: one address register each
-// instead of two (system_of admits a system only if they reach every array).
+// instead of two (fused_groups admits a system only if they reach every array).
 struct F3 { float v[3]; };
 struct F9 { float v[9]; };
 struct U5 { uint32_t v[5]; };
