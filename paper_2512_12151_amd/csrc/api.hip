@@ -197,14 +197,12 @@ bf_status step_assemble(bf_problem* pb, bool bf16) {
   int npat = n;
   int* vcnt = pb->vcnt.as<int>();
   int* lcnt = pb->lcnt.as<int>();
-  int* wmax = pb->scratch_int.as<int>();   // free after the per-mesh setup
   {
     ZeroList z;
     z.add(flags, 4 * 16);
     z.add(pb->viol_part.p, 4 * 2);
     z.add(vcnt, 4LL * N);
     z.add(lcnt, 4LL * N);
-    z.add(wmax, 4 * 2);
     zero_many(z, s);
   }
   HIPCHK(c, hipEventRecord(pb->ev[0], s));
@@ -288,8 +286,8 @@ bf_status step_assemble(bf_problem* pb, bool bf16) {
     return BF_OK;
   };
   const bool two_kernels = pcg_fused_groups(N) == 0;
+  launch_slice_widths(N, nslices, row_ptr, lptr, sbu, sbl, s);
   if (nslices <= kOffsetSlices) {
-    launch_slice_widths(N, nslices, row_ptr, lptr, sbu, sbl, nullptr, s);
     launch_slice_offsets(nslices, sbu, sbl, pb->host_slots, s);
     if (two_kernels) {
       const bf_status r0 = copy_offsets();
@@ -298,15 +296,17 @@ bf_status step_assemble(bf_problem* pb, bool bf16) {
     HIPCHK(c, hipStreamSynchronize(s));
     for (int k = 0; k < 4; ++k) tot[k] = pb->host_slots[k];
   } else {
-    launch_slice_widths(N, nslices, row_ptr, lptr, sbu, sbl, wmax, s);
     scan_exclusive(sbu, sbu, nslices, sbu + nslices, tmp, s);
     scan_exclusive(sbl, sbl, nslices, sbl + nslices, tmp, s);
     const bf_status r0 = copy_offsets();
     if (r0 != BF_OK) return r0;
-    HIPCHK(c, hipMemcpyAsync(&tot[2], wmax, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
     tot[0] = pb->h_sbu[nslices];
     tot[1] = pb->h_sbl[nslices];
+    for (int k = 0; k < nslices; ++k) {
+      tot[2] = std::max(tot[2], (pb->h_sbu[k + 1] - pb->h_sbu[k]) / kSlice);
+      tot[3] = std::max(tot[3], (pb->h_sbl[k + 1] - pb->h_sbl[k]) / kSlice);
+    }
   }
   pb->nslot_u = tot[0];
   pb->nslot_l = tot[1];

@@ -278,7 +278,7 @@ __device__ inline uint32_t bf16_rne(float f) {
 // A wavefront per slice, a lane per row.
 __global__ void __launch_bounds__(kBlock)
 k_slice_widths(int N, int nslices, const int* __restrict__ row_ptr, const int* __restrict__ lptr,
-               int* __restrict__ cu, int* __restrict__ cl, int* __restrict__ wmax) {
+               int* __restrict__ cu, int* __restrict__ cl) {
   const int r = blockIdx.x * kBlock + threadIdx.x, sl = r / kSlice;
   if (sl >= nslices) return;
   int wu = r < N ? row_ptr[r + 1] - row_ptr[r] - 1 : 0, wl = r < N ? lptr[r + 1] - lptr[r] : 0;
@@ -290,10 +290,6 @@ k_slice_widths(int N, int nslices, const int* __restrict__ row_ptr, const int* _
   if (r % kSlice) return;
   cu[sl] = wu * kSlice;
   cl[sl] = wl * kSlice;
-  if (wmax) {
-    atomicMax(&wmax[0], wu);
-    atomicMax(&wmax[1], wl);
-  }
 }
 
 // Both scans of the widths and what the host has to know of them, out[4] =
@@ -456,10 +452,9 @@ void launch_lower_fill(int N, const int* row_ptr, const int* col, const int* lpt
   hipLaunchKernelGGL(k_lower_fill, dim3(div_up(N, kBlock)), dim3(kBlock), 0, s, N, row_ptr, col, lptr, lcur, lsrc);
 }
 
-void launch_slice_widths(int N, int nslices, const int* row_ptr, const int* lptr, int* cu, int* cl, int* wmax,
-                         hipStream_t s) {
+void launch_slice_widths(int N, int nslices, const int* row_ptr, const int* lptr, int* cu, int* cl, hipStream_t s) {
   hipLaunchKernelGGL(k_slice_widths, dim3(div_up((long long)nslices * kSlice, kBlock)), dim3(kBlock), 0, s, N, nslices,
-                     row_ptr, lptr, cu, cl, wmax);
+                     row_ptr, lptr, cu, cl);
 }
 
 void launch_slice_offsets(int nslices, int* cu, int* cl, int* out, hipStream_t s) {

@@ -378,8 +378,7 @@ void launch_lower_fill(int N, const int* row_ptr, const int* col, const int* lpt
 // slots, upper and lower, and the largest widths.
 constexpr int kOffsetSlices = 1024;
 void launch_slice_offsets(int nslices, int* cu, int* cl, int* out, hipStream_t s);
-void launch_slice_widths(int N, int nslices, const int* row_ptr, const int* lptr, int* cu, int* cl, int* wmax,
-                         hipStream_t s);
+void launch_slice_widths(int N, int nslices, const int* row_ptr, const int* lptr, int* cu, int* cl, hipStream_t s);
 // The SpMV visits upper and lower slots in pairs, kPairs per step, and reads
 // up to (max width + kPairs) * kSlice slots past the end of a slice's range;
 // the slot arrays carry that much zeroed padding after their last slot.
