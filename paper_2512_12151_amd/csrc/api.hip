@@ -798,11 +798,11 @@ bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* o, double* p_out, 
   } else {
     // Flexible CG on the FP32-stored system in FP64 vectors (the refinement):
     // every sweep forms the true residual r = b_hat - H_hat x in FP64, solves
-    // H_bf16 z = r by the two-kernel PCG on the BF16 blocks to the relative
-    // tolerance tol (a BF16 breakdown ends that inner solve early: BF16
-    // rounding can make the scaled matrix indefinite in its lowest modes),
-    // makes z conjugate (in H_hat) to the last kFcgWindow directions, and
-    // takes the exact step along it.  The outer Krylov recurrence on the FP32
+    // H_bf16 z = r by the PCG on the BF16 blocks to the relative tolerance tol
+    // (a BF16 breakdown ends that inner solve early: BF16 rounding can make the
+    // scaled matrix indefinite in its lowest modes), makes z conjugate (in
+    // H_hat) to the last kFcgWindow - 1 directions (directions.h), and takes
+    // the exact step along it.  The outer Krylov recurrence on the FP32
     // operator recovers the modes the BF16 blocks cannot resolve.
     constexpr int kFcgWindow = Directions::kMax;
     const long long n3 = 3LL * S.N4;
@@ -845,7 +845,7 @@ bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* o, double* p_out, 
       if (r0 != BF_OK) return r0;
       if (pb->host_sc->iter > 0) launch_pcg_flush(S16, s);
       const double* z = pb->host_sc->iter > 0 ? S16.x : rd;   // no progress: steepest descent
-      // p = z - sum_j (z.q_j / p_j.q_j) p_j over the window
+      // p = z - sum_j (z.q_j / p_j.q_j) p_j over the ring
       const int nwin = std::min(sweeps, kFcgWindow);
       double* P = Pv(sweeps);
       double* Q = Qv(sweeps);
@@ -857,9 +857,7 @@ bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* o, double* p_out, 
         HIPCHK(c, hipStreamSynchronize(s));
         for (int j = 0; j < nwin; ++j) {
           const double pqj = pq_hist[(sweeps - 1 - j) % kFcgWindow];
-          if (!(pqj > 0.0)) continue;
-          dir.a[dir.n] = -dots[j] / pqj;
-          dir.p[dir.n++] = Pv(sweeps - 1 - j);
+          if (pqj > 0.0) dir.add(-dots[j] / pqj, Pv(sweeps - 1 - j), P);
         }
       }
       launch_direction((int)n3, z, dir, P, s);

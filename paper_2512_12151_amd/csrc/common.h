@@ -10,6 +10,7 @@
 
 #include "../../include/bfal.h"
 #include "../../include/bfal_host.h"
+#include "directions.h"
 
 namespace bfal {
 
@@ -445,13 +446,7 @@ void launch_pcg_init_from64(const PcgSystem& S, const double* rd, const double* 
 void launch_apply64(const PcgSystem& S, const double* xd, double* yd, hipStream_t s);
 void launch_dots64(int n3, const double* a, const double* const* b, int nb, double* part, double* out,
                    hipStream_t s);
-// out = z + sum a_j p_j (FP64), the terms added in their order.
-struct Directions {
-  static constexpr int kMax = 4;
-  int n = 0;
-  double a[kMax];
-  const double* p[kMax];
-};
+// out = z + sum a_j p_j (directions.h).
 void launch_direction(int n3, const double* z, const Directions& d, double* out, hipStream_t s);
 void launch_axpy_d(int n3, double alpha, const double* x, double* y, hipStream_t s);
 void launch_pcg_finish64(const PcgSystem& S, const double* Linv, const double* xd, double* pout,

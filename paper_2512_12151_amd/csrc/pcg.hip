@@ -815,9 +815,9 @@ k_axpy_d(int n3, double alpha, const double* __restrict__ x, double* __restrict_
 
 // out = z + a_0 p_0 + a_1 p_1 + ... in this order, in one pass: the copy and an
 // axpy per direction were five launches and eleven passes.  A direction that
-// lies in out itself (the oldest one's buffer is the new one's) stands for the
-// sum so far: its term only scales the result.  (24.5k nodes: 3.6 us; before,
-// a copy of 2.9 and up to four passes of 2.4, and a launch's gap each.)
+// lies in out itself stands for the sum so far (directions.h).  (24.5k nodes:
+// 3.6 us; before, a copy of 2.9 and up to four passes of 2.4, and a launch's
+// gap each.)
 __global__ void __launch_bounds__(kVecBlock)
 k_direction(int n3, const double* __restrict__ z, Directions d, double* out) {
   for (int i = blockIdx.x * kVecBlock + threadIdx.x; i < n3; i += gridDim.x * kVecBlock) {
