@@ -170,10 +170,11 @@ bf_status problem_init(bf_context* c, bf_problem* pb, const bf_mesh_desc* m, int
     if (!e) HIPCHK(c, hipEventCreate(&e));
   if (!pb->host_sc) {
     static_assert(sizeof(PcgScalars) % sizeof(unsigned long long) == 0, "host_stat follows the scalars");
-    HIPCHK(c, hipHostMalloc((void**)&pb->host_sc, sizeof(PcgScalars) + 13 * sizeof(unsigned long long), hipHostMallocDefault));
+    HIPCHK(c, hipHostMalloc((void**)&pb->host_sc, sizeof(PcgScalars) + (kSolveWords + 2 + 8) * sizeof(unsigned long long),
+                            hipHostMallocDefault));
     pb->host_stat = reinterpret_cast<unsigned long long*>(pb->host_sc + 1);
-    pb->host_slots = reinterpret_cast<int*>(pb->host_stat + 3);
-    pb->host_sums = reinterpret_cast<double*>(pb->host_stat + 5);
+    pb->host_slots = reinterpret_cast<int*>(pb->host_stat + kSolveWords);
+    pb->host_sums = reinterpret_cast<double*>(pb->host_stat + kSolveWords + 2);
   }
   ALLOC(c, pb->scal, sizeof(PcgScalars));
   HIPCHK(c, hipMemsetAsync(pb->scal.p, 0, sizeof(PcgScalars), s));
@@ -677,7 +678,8 @@ bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* o, double* p_out, 
   HIPCHK(c, hipSetDevice(c->device));
   hipStream_t s = c->stream;
   const int N = pb->N, n = pb->n_c;
-  int* flags = pb->flags.as<int>();
+  // an error that the caller's thread has pending from before is not the step's: it is left there
+  const bool clean = hipPeekAtLastError() == hipSuccess;
   {
     const bf_status r0 = step_assemble(pb, bf16);
     if (r0 != BF_OK) return r0;
@@ -695,55 +697,60 @@ bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* o, double* p_out, 
   }
   int launched = 0, total_iters = 0, timed = 0, replacements = 0;
   bool assembly_checked = false;
-  // A one-kernel solve: kept some launches ahead of what the device has
-  // reported into pinned memory, so that neither side waits and few launches
-  // follow the end.  Sets host_sc->iter.  Where the system's workgroups fit the
-  // chip the launches are, in turn, the state that starts a solve, as many
-  // steps as there are up to a replacement, and the replacement: each does
-  // nothing where the state is another's.  Launches that are timed, and a
-  // solve whose workgroups did not get the chip to themselves, take one
+  // A one-kernel solve (follow_solve).  Sets host_sc->iter.  Where the system's
+  // workgroups fit the chip the launches are, in turn, the state that starts a
+  // solve, as many steps as there are up to a replacement, and the replacement:
+  // each does nothing where the state is another's.  Launches that are timed,
+  // and a solve whose workgroups did not get the chip to themselves, take one
   // iteration each.
-  constexpr int kFusedAhead = 12, kResidentAhead = 4, kResidentSteps = 4096;
-  auto run_fused = [&](PcgSystem Sx, bool use_bf16) -> bf_status {
-    volatile unsigned long long* st = pb->host_stat;
-    st[0] = st[1] = st[2] = 0;
-    Sx.hstat = pb->host_stat;
-    bool res = pcg_resident(Sx, c->num_cu);
-    long long mine = 0, spins = 0;
-    for (;;) {
-      const unsigned long long w = st[0];
-      const unsigned end = (unsigned)(w & 0xffffffffu);
-      if (end) {
-        if (end == kEndAssembly) {
-          int hf = 0;
-          bf_status r0 = read_flags(pb, &hf);
-          return r0 != BF_OK ? r0 : flags_to_status(c, hf);
-        }
-        if (end == kEndStuck) {
-          (void)hipStreamSynchronize(s);
-          return fail(c, BF_ERR_HIP, "the solve's workgroups lost each other");
-        }
-        break;
-      }
-      if (res && st[2]) res = false;
-      if (mine - (long long)(w >> 32) < (res ? kResidentAhead : kFusedAhead)) {
-        const bool t = launched < ntime;
-        Sx.report_mask = res ? 0 : 3;
-        if (res && !t && mine % 3 == 1)
-          launch_pcg_resident(Sx, use_bf16, (int)(mine & 1), kResidentSteps, s);
-        else
-          launch_pcg_fused(Sx, use_bf16, (int)(mine & 1), s, t ? pb->tev[2 * launched] : nullptr,
-                           t ? pb->tev[2 * launched + 1] : nullptr);
-        if (mine == 0) HIPCHK(c, hipGetLastError());
-        ++launched;
-        ++mine;
-        spins = 0;
-      } else if ((++spins & 0xfff) == 0) {   // the device stays behind: is the stream still sound?
-        const hipError_t e = hipStreamQuery(s);
-        if (e != hipSuccess && e != hipErrorNotReady) HIPCHK(c, e);
-      }
+  constexpr int kResidentSteps = 4096;
+  struct SolveDevice {
+    PcgSystem S;
+    bool bf16;
+    int& launched;   // (of all solves of the step)
+    int ntime;
+    const std::vector<hipEvent_t>& tev;
+    hipStream_t s;
+    hipError_t err;
+
+    bool launch(long long number, bool resident) {
+      const bool t = launched < ntime;
+      S.report_mask = resident ? 0 : 3;
+      const int par = (int)(number & 1);
+      err = resident && !t && number % 3 == 1
+                ? launch_pcg_resident(S, bf16, par, kResidentSteps, s)
+                : launch_pcg_fused(S, bf16, par, s, t ? tev[2 * launched] : nullptr, t ? tev[2 * launched + 1] : nullptr);
+      if (err == hipSuccess) ++launched;
+      return err == hipSuccess;
     }
-    pb->host_sc->iter = (int)st[1];
+    StreamState query() {
+      err = hipStreamQuery(s);
+      return err == hipSuccess ? StreamState::kIdle : err == hipErrorNotReady ? StreamState::kBusy : StreamState::kError;
+    }
+  };
+  auto run_fused = [&](const PcgSystem& Sx, bool use_bf16) -> bf_status {
+    if (clean) HIPCHK(c, hipGetLastError());   // of the launches so far
+    SolveDevice dev{Sx, use_bf16, launched, ntime, pb->tev, s, hipSuccess};
+    dev.S.hstat = pb->host_stat;
+    switch (follow_solve(dev, pb->host_stat, pcg_resident(Sx, c->num_cu))) {
+      case SolveEnd::kError:
+        if (clean) (void)hipGetLastError();
+        HIPCHK(c, dev.err);
+        break;
+      case SolveEnd::kLost: return fail(c, BF_ERR_HIP, "the solve's launches ended without an end of the solve");
+      case SolveEnd::kEnded: break;
+    }
+    const int end = (int)(unsigned)pb->host_stat[kWordState];
+    if (end == kEndAssembly) {
+      int hf = 0;
+      const bf_status r0 = read_flags(pb, &hf);
+      return r0 != BF_OK ? r0 : flags_to_status(c, hf);
+    }
+    if (end == kEndStuck) {
+      (void)hipStreamSynchronize(s);
+      return fail(c, BF_ERR_HIP, "the solve's workgroups lost each other");
+    }
+    pb->host_sc->iter = (int)pb->host_stat[kWordIter];
     timed = std::max(timed, std::min(ntime, launched));
     total_iters += pb->host_sc->iter;
     return BF_OK;

@@ -11,6 +11,7 @@
 #include "../../include/bfal.h"
 #include "../../include/bfal_host.h"
 #include "directions.h"
+#include "solve_loop.h"
 
 namespace bfal {
 
@@ -30,8 +31,6 @@ constexpr int kBlock = 256;        // default workgroup size (4 waves)
 
 // State of a one-kernel PCG solve between launches (pcg_fused.hip).
 enum : int { kNormal = 0, kTested = 1, kFresh = 2, kReplace = 3 };
-// How a one-kernel solve ended; the first two are the values of PcgScalars::done.
-enum : int { kEndConverged = 1, kEndMaxIter = 2, kEndBreakdown = 8, kEndAssembly = 16, kEndStuck = 32 };
 struct PcgCtl {
   int k;             // iteration of the state
   int mode;          // kNormal, kTested, kFresh or kReplace
@@ -144,7 +143,7 @@ struct PcgSystem {
   const float* bhat;
   const int* aflags;             // the assembly's error flags, or null
   const int* nnzb;               // its block count
-  unsigned long long* hstat;     // pinned host words: launches << 32 | end code, iteration of the end, PcgCtl::apart; or null
+  unsigned long long* hstat;     // pinned host words (solve_loop.h), or null
   int report_mask;               // launches with (number & mask) == 0 report, and the end does
 };
 
@@ -416,16 +415,17 @@ void launch_pcg_iteration_batched(const PcgSystem* sys, const int* wg_sys_spmv, 
 // pcg_fused.hip: the iteration in one kernel.  Workgroups of a system (0: it
 // takes the two kernels), one launch, and one launch for several systems.
 // par alternates 0, 1, 0, ... over the launches of a solve (of a batch), from
-// either value.
+// either value; where one fails (the status is the launch's own) no further one
+// may follow, as it would read the state that the failed one was to write.
 int pcg_fused_groups(int N);
-void launch_pcg_fused(const PcgSystem& S, bool bf16, int par, hipStream_t s, hipEvent_t t0 = nullptr,
-                      hipEvent_t t1 = nullptr);
+hipError_t launch_pcg_fused(const PcgSystem& S, bool bf16, int par, hipStream_t s, hipEvent_t t0 = nullptr,
+                            hipEvent_t t1 = nullptr);
 // The resident form: one launch that makes up to `steps` iterations of a solve
 // whose workgroups all fit the chip (pcg_resident).  It leaves the states that
 // start, resume or replace a residual to launch_pcg_fused.
 bool pcg_resident(const PcgSystem& S, int num_cu);
-void launch_pcg_resident(const PcgSystem& S, bool bf16, int par, int steps, hipStream_t s);
-void launch_pcg_fused_batched(const PcgSystem* sys, const int* wg_sys, int nwg, int par, hipStream_t s);
+hipError_t launch_pcg_resident(const PcgSystem& S, bool bf16, int par, int steps, hipStream_t s);
+hipError_t launch_pcg_fused_batched(const PcgSystem* sys, const int* wg_sys, int nwg, int par, hipStream_t s);
 // x += the directions the update kernel has not applied yet (before x is read).
 void launch_pcg_flush(const PcgSystem& S, hipStream_t s);
 // p = L^{-T} x in FP64 and the stats (max |p|, max violation).

@@ -112,10 +112,10 @@ __device__ __forceinline__ unsigned* start_word(const PcgSystem& S, int par) {
 __device__ __forceinline__ void report(const PcgSystem& S, int launches, int done, int k) {
   if (!S.hstat || (!done && (launches & S.report_mask))) return;
   if (done) {
-    __hip_atomic_store(&S.hstat[1], (unsigned long long)(unsigned)k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&S.hstat[kWordIter], (unsigned long long)(unsigned)k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __threadfence_system();
   }
-  __hip_atomic_store(&S.hstat[0], ((unsigned long long)(unsigned)launches << 32) | (unsigned)done, __ATOMIC_RELAXED,
+  __hip_atomic_store(&S.hstat[kWordState], ((unsigned long long)(unsigned)launches << 32) | (unsigned)done, __ATOMIC_RELAXED,
                      __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
@@ -692,7 +692,7 @@ __device__ __forceinline__ void resident(const PcgSystem& S, PcgCtl c, int s, in
   if (!all_started(S, par)) {
     if (leader) {
       c.apart = 1;
-      if (S.hstat) __hip_atomic_store(&S.hstat[2], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      if (S.hstat) __hip_atomic_store(&S.hstat[kWordApart], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       hand_on(S, c, par);
     }
     return;
@@ -709,7 +709,7 @@ __device__ __forceinline__ void resident(const PcgSystem& S, PcgCtl c, int s, in
     __syncthreads();
     if (__builtin_expect(sh.stuck, 0)) {
       if (t == 0 && S.hstat)
-        __hip_atomic_store(&S.hstat[0], (unsigned long long)kEndStuck, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&S.hstat[kWordState], (unsigned long long)kEndStuck, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       return;
     }
     F3 qu[kP], ql[kP];
@@ -882,18 +882,13 @@ int pcg_fused_groups(int N) {
   return nslices <= kFusedMaxSlices ? nslices : 0;
 }
 
-void launch_pcg_fused(const PcgSystem& S, bool bf16, int par, hipStream_t s, hipEvent_t t0, hipEvent_t t1) {
+hipError_t launch_pcg_fused(const PcgSystem& S, bool bf16, int par, hipStream_t s, hipEvent_t t0, hipEvent_t t1) {
+  const void* f = bf16 ? reinterpret_cast<const void*>(k_fused<uint32_t>) : reinterpret_cast<const void*>(k_fused<float>);
+  PcgSystem Sx = S;
+  void* args[] = {&Sx, &par};
   const dim3 grid(S.fused_nwg), block(kFusedBlock);
-  if (t0 && t1) {
-    if (bf16)
-      hipExtLaunchKernelGGL(k_fused<uint32_t>, grid, block, 0, s, t0, t1, 0, S, par);
-    else
-      hipExtLaunchKernelGGL(k_fused<float>, grid, block, 0, s, t0, t1, 0, S, par);
-  } else if (bf16) {
-    hipLaunchKernelGGL(k_fused<uint32_t>, grid, block, 0, s, S, par);
-  } else {
-    hipLaunchKernelGGL(k_fused<float>, grid, block, 0, s, S, par);
-  }
+  return t0 && t1 ? hipExtLaunchKernel(f, grid, block, args, 0, s, t0, t1, 0)
+                  : hipLaunchKernel(f, grid, block, args, 0, s);
 }
 
 // Two of its workgroups fit a compute unit (128 registers a thread, 47 KB of
@@ -901,16 +896,18 @@ void launch_pcg_fused(const PcgSystem& S, bool bf16, int par, hipStream_t s, hip
 // every size (see above), so there is no other bound.
 bool pcg_resident(const PcgSystem& S, int num_cu) { return S.fused_nwg > 0 && S.fused_nwg + kCollectors <= 2 * num_cu; }
 
-void launch_pcg_resident(const PcgSystem& S, bool bf16, int par, int steps, hipStream_t s) {
-  const dim3 grid(S.fused_nwg + kCollectors), block(kResBlock);
-  if (bf16)
-    hipLaunchKernelGGL(k_resident<uint32_t>, grid, block, 0, s, S, par, steps);
-  else
-    hipLaunchKernelGGL(k_resident<float>, grid, block, 0, s, S, par, steps);
+hipError_t launch_pcg_resident(const PcgSystem& S, bool bf16, int par, int steps, hipStream_t s) {
+  const void* f =
+      bf16 ? reinterpret_cast<const void*>(k_resident<uint32_t>) : reinterpret_cast<const void*>(k_resident<float>);
+  PcgSystem Sx = S;
+  void* args[] = {&Sx, &par, &steps};
+  return hipLaunchKernel(f, dim3(S.fused_nwg + kCollectors), dim3(kResBlock), args, 0, s);
 }
 
-void launch_pcg_fused_batched(const PcgSystem* sys, const int* wg_sys, int nwg, int par, hipStream_t s) {
-  hipLaunchKernelGGL(k_fused_batched<float>, dim3(nwg), dim3(kFusedBlock), 0, s, sys, wg_sys, par);
+hipError_t launch_pcg_fused_batched(const PcgSystem* sys, const int* wg_sys, int nwg, int par, hipStream_t s) {
+  void* args[] = {&sys, &wg_sys, &par};
+  return hipLaunchKernel(reinterpret_cast<const void*>(k_fused_batched<float>), dim3(nwg), dim3(kFusedBlock), args, 0,
+                         s);
 }
 
 }  // namespace bfal

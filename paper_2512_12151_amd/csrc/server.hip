@@ -350,17 +350,19 @@ void batch_loop(bf_server* sv) {
     }
     const PcgSystem* sys = sv->sys_dev.as<PcgSystem>();
     const int* map = sv->map_spmv.as<int>();
-    for (int k = 0; k < sv->iters_per_round; ++k) {
-      if (nwg_fused) launch_pcg_fused_batched(sys, map + nwg_spmv + nwg_vec, nwg_fused, sv->par, s);
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < sv->iters_per_round && e == hipSuccess; ++k) {
+      if (nwg_fused) e = launch_pcg_fused_batched(sys, map + nwg_spmv + nwg_vec, nwg_fused, sv->par, s);
       sv->par ^= 1;
       if (nwg_spmv) launch_pcg_iteration_batched(sys, map, nwg_spmv, map + nwg_spmv, nwg_vec, false, s);
     }
     const int n = (int)sv->active.size();
     hipLaunchKernelGGL(k_gather_status, dim3(div_up(n, kBlock)), dim3(kBlock), 0, s, sys, n,
                        sv->status_dev.as<int>());
-    hipError_t e = hipMemcpyAsync(sv->h_status, sv->status_dev.p, sizeof(int) * kStatusInts * n,
-                                  hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(sv->h_status, sv->status_dev.p, sizeof(int) * kStatusInts * n, hipMemcpyDeviceToHost, s);
+    const hipError_t es = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = es;
     if (e != hipSuccess) {
       c->err = hipGetErrorString(e);
       for (int si : sv->active) {

@@ -189,3 +189,19 @@ def test_sliced_storage_at_the_edges_of_its_scans(name, cells):
     """The solution against the assembled matrix, which is read from the row
     storage: a wrong slot offset would leave a block out of the product."""
     test_solution_of_the_assembled_system(name, lambda: _box(*cells), 1)
+
+
+def test_an_older_error_of_the_thread_is_not_the_solves():
+    """A failed HIP call of the program's own leaves an error pending on its
+    thread: the solve neither reports it as its own nor takes it away."""
+    import ctypes
+    pb = bfal.Problem.from_scene(bfal.Context(0), _box(2, 2, 6))
+    p, _, status = pb.newton_step(tol=1e-5)
+    hip = ctypes.CDLL("libamdhip64.so")   # the one that is loaded already
+    bad = hip.hipSetDevice(10 ** 6)
+    pending = hip.hipPeekAtLastError()
+    q, _, status2 = pb.newton_step(tol=1e-5)
+    after = hip.hipGetLastError()
+    print("the call's error", bad, "pending before", pending, "after", after, flush=True)
+    assert bad != 0 and status == status2 == 0 and np.array_equal(p, q)
+    assert after == pending

@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="no host compiler")
-@pytest.mark.parametrize("driver", ["directions_driver"])
+@pytest.mark.parametrize("driver", ["directions_driver", "solve_loop_driver"])
 def test_under_asan_and_ubsan(tmp_path, driver):
     exe = str(tmp_path / driver)
     cmd = ["g++", "-std=c++17", "-O1", "-g", "-Wall", "-Wextra", "-Werror", "-fno-omit-frame-pointer",
