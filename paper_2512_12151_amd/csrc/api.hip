@@ -728,6 +728,8 @@ bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* o, double* p_out, 
       return err == hipSuccess ? StreamState::kIdle : err == hipErrorNotReady ? StreamState::kBusy : StreamState::kError;
     }
   };
+  pb->host_stat[kWordStuck] = 0;   // (the stream was waited for in the assembly)
+  auto stuck = [&]() { return fail(c, BF_ERR_HIP, "the solve's workgroups lost each other"); };
   auto run_fused = [&](const PcgSystem& Sx, bool use_bf16) -> bf_status {
     if (clean) HIPCHK(c, hipGetLastError());   // of the launches so far
     SolveDevice dev{Sx, use_bf16, launched, ntime, pb->tev, s, hipSuccess};
@@ -737,6 +739,7 @@ bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* o, double* p_out, 
         if (clean) (void)hipGetLastError();
         HIPCHK(c, dev.err);
         break;
+      case SolveEnd::kStuck: (void)hipStreamSynchronize(s); return stuck();
       case SolveEnd::kLost: return fail(c, BF_ERR_HIP, "the solve's launches ended without an end of the solve");
       case SolveEnd::kEnded: break;
     }
@@ -745,10 +748,6 @@ bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* o, double* p_out, 
       int hf = 0;
       const bf_status r0 = read_flags(pb, &hf);
       return r0 != BF_OK ? r0 : flags_to_status(c, hf);
-    }
-    if (end == kEndStuck) {
-      (void)hipStreamSynchronize(s);
-      return fail(c, BF_ERR_HIP, "the solve's workgroups lost each other");
     }
     pb->host_sc->iter = (int)pb->host_stat[kWordIter];
     timed = std::max(timed, std::min(ntime, launched));
@@ -887,6 +886,7 @@ bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* o, double* p_out, 
   const double refine_rr = pb->host_sc->rr_true, refine_bb = pb->host_sc->bb;
   HIPCHK(c, hipMemcpyAsync(pb->host_sc, S.sc, sizeof(PcgScalars), hipMemcpyDeviceToHost, s));
   HIPCHK(c, hipStreamSynchronize(s));
+  if (pb->host_stat[kWordStuck]) return stuck();
   const int nnzb = pb->host_sc->nnzb, hflags = pb->host_sc->aflags;
   pb->nnzb_last = nnzb;
   pb->stepped = true;

@@ -527,6 +527,14 @@ __device__ __forceinline__ bool read_totals(Buffer b, int k, int copy, int lane,
   return true;
 }
 
+// A workgroup stops without having handed on a state: the host is told, and
+// the launches queued behind find both copies of the state ended.
+__device__ __forceinline__ void give_up(const PcgSystem& S) {
+  if (S.hstat) __hip_atomic_store(&S.hstat[kWordStuck], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __threadfence_system();
+  S.sc->ctl[0].done = S.sc->ctl[1].done = kEndStuck;
+}
+
 // What follows from the totals of state c.k: the step's alpha and beta and the
 // next state, or false and in c how the solve or this stretch of it ended.
 __device__ __forceinline__ bool advance(const PcgSystem& S, PcgCtl& c, double v, bool leader, float& alpha,
@@ -708,8 +716,7 @@ __device__ __forceinline__ void resident(const PcgSystem& S, PcgCtl c, int s, in
     }
     __syncthreads();
     if (__builtin_expect(sh.stuck, 0)) {
-      if (t == 0 && S.hstat)
-        __hip_atomic_store(&S.hstat[kWordState], (unsigned long long)kEndStuck, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      if (t == 0) give_up(S);
       return;
     }
     F3 qu[kP], ql[kP];

@@ -9,12 +9,15 @@ enum : int { kEndConverged = 1, kEndMaxIter = 2, kEndBreakdown = 8, kEndAssembly
 
 // The words in pinned memory that the device reports into (PcgSystem::hstat):
 // launches made << 32 | end code (0 while the solve runs), the iteration of the
-// end, and whether the resident kernel found its workgroups not all running.
-enum : int { kWordState = 0, kWordIter = 1, kWordApart = 2, kSolveWords = 3 };
+// end, whether the resident kernel found its workgroups not all running, and
+// whether one of them gave up waiting for the others (a word of its own: the
+// launches queued behind go on reporting into the first).
+enum : int { kWordState = 0, kWordIter = 1, kWordApart = 2, kWordStuck = 3, kSolveWords = 4 };
 
 enum class StreamState { kBusy, kIdle, kError };
 enum class SolveEnd {
   kEnded,     // the device reported an end: its code is in kWordState
+  kStuck,     // a workgroup gave up: the vectors hold no state of the solve
   kError,     // a launch or the stream failed
   kLost,      // all launches are complete and no end was reported
 };
@@ -30,15 +33,19 @@ constexpr int kSpinsPerQuery = 4096;
 // state that the next launch reads is then missing: no further one may follow);
 // StreamState query() of the stream.  Every wait ends: a device that stays
 // behind is asked for, and where its stream is idle on two askings with no
-// report between that would let the host go on, the solve is lost.
+// report between that would let the host go on, the solve is lost.  kWordStuck
+// is the caller's to clear and to look at once more when the stream has been
+// waited for: a workgroup may give up after the solve's leader has gone on.
 template <class Device>
 SolveEnd follow_solve(Device& dev, volatile unsigned long long* word, bool resident) {
-  for (int k = 0; k < kSolveWords; ++k) word[k] = 0;
+  word[kWordState] = word[kWordIter] = word[kWordApart] = 0;
   long long launched = 0, spins = 0;
   bool idle = false;
   for (;;) {
     const unsigned long long state = word[kWordState];
-    if ((unsigned)state) return SolveEnd::kEnded;
+    const unsigned end = (unsigned)state;
+    if (word[kWordStuck] || end == kEndStuck) return SolveEnd::kStuck;
+    if (end) return SolveEnd::kEnded;
     if (resident && word[kWordApart]) resident = false;
     if (launched - (long long)(state >> 32) < (resident ? kResidentAhead : kAhead)) {
       if (!dev.launch(launched, resident)) return SolveEnd::kError;

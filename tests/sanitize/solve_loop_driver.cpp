@@ -24,10 +24,11 @@ int failures = 0;
 constexpr long long kNever = 1LL << 40;
 
 struct Model {
-  volatile unsigned long long word[kSolveWords] = {7, 7, 7};   // a solve before this one left them
+  volatile unsigned long long word[kSolveWords] = {7, 7, 7, 0};   // a solve before this one left them (the last is the caller's)
   long long end_at = kNever;      // the launch that ends the solve
   long long fail_at = kNever;     // the launch that fails
   long long silent_at = kNever;   // from this launch on nothing is reported
+  long long stuck_at = kNever;    // the launch whose workgroups lose each other; those behind it report all the same
   long long apart_at = kNever;    // the launch that finds its workgroups not all running
   int query_error_after = 1 << 30;
   bool lazy = false;              // launches run when the stream is asked, and not before
@@ -40,6 +41,10 @@ struct Model {
   void run_queued() {
     for (; ran < asked; ++ran) {
       if (ran == apart_at) word[kWordApart] = 1;
+      if (ran == stuck_at) {
+        word[kWordStuck] = 1;
+        continue;
+      }
       if (ran >= silent_at) continue;
       if (ran == end_at) word[kWordIter] = 41;
       const int mask = resident ? 0 : 3;
@@ -117,6 +122,16 @@ int main() {
         m.busy = true;
         EXPECT(follow_solve(m, m.word, resident) == SolveEnd::kError);
       }
+    }
+  for (bool lazy : {false, true})
+    for (long long end_at : {kNever, 6LL, 7LL, 9LL}) {   // (a mixed state that seems to have converged, too)
+      const char* name = "stuck";
+      Model m;
+      m.stuck_at = 5;   // (not the last of the launches that are queued together)
+      m.end_at = end_at;
+      m.lazy = lazy;
+      EXPECT(follow_solve(m, m.word, true) == SolveEnd::kStuck);
+      EXPECT(m.asked <= 6 + kResidentAhead);
     }
   for (bool lazy : {false, true}) {
     const char* name = "apart";
