@@ -188,6 +188,16 @@ bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* opts, double* p_ou
 bf_status bf_get_gradient(bf_problem* pb, double* g_out);
 /* Number of stored upper blocks (diagonal included) of the last step. */
 bf_status bf_get_nnzb(bf_problem* pb, int64_t* nnzb);
+/* Which way the last step's PCG iterations were made (all zero where none of
+ * them stayed in the resident kernel: systems too large for it, timed
+ * iterations). */
+typedef struct {
+  int32_t resident_iters;    /* iterations made in launches of the resident kernel */
+  int32_t resident_launches; /* its launches that made any */
+  int32_t apart;             /* solves that went on by one launch per iteration because its workgroups did not
+                                all find room on the device at once */
+} bf_solver_path;
+bf_status bf_get_solver_path(bf_problem* pb, bf_solver_path* out);
 /* Upper BSR pattern: row_ptr [n_nodes+1], col [nnzb]; emap [n_tets][10] and
  * cmap [n_pt+n_ee][10] slots of the local vertex pairs (0,0),(0,1),(0,2),(0,3),
  * (1,1),(1,2),(1,3),(2,2),(2,3),(3,3) (the block is transposed when the first

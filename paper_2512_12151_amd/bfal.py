@@ -54,6 +54,10 @@ class bf_step_stats(C.Structure):
         return d
 
 
+class bf_solver_path(C.Structure):
+    _fields_ = [("resident_iters", C.c_int32), ("resident_launches", C.c_int32), ("apart", C.c_int32)]
+
+
 class BfalError(RuntimeError):
     def __init__(self, status, msg):
         super().__init__(f"{STATUS.get(status, status)}: {msg}")
@@ -126,6 +130,7 @@ _PROTOS = [
                                  C.POINTER(bf_step_stats)]),
     ("bf_get_gradient", C.c_int, [C.c_void_p, C.c_void_p]),
     ("bf_get_nnzb", C.c_int, [C.c_void_p, C.POINTER(C.c_int64)]),
+    ("bf_get_solver_path", C.c_int, [C.c_void_p, C.POINTER(bf_solver_path)]),
     ("bf_get_pattern", C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
     ("bf_get_blocks", C.c_int, [C.c_void_p, C.c_void_p]),
     ("bf_footprint_bytes", C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_size_t)]),
@@ -396,6 +401,12 @@ class Problem:
         n = C.c_int64()
         self.ctx.check(lib().bf_get_nnzb(self.h, C.byref(n)))
         return int(n.value)
+
+    def solver_path(self):
+        """How the last step's PCG iterations were made (bf_solver_path)."""
+        o = bf_solver_path()
+        self.ctx.check(lib().bf_get_solver_path(self.h, C.byref(o)))
+        return {k: int(getattr(o, k)) for k, _ in o._fields_}
 
     def pattern(self):
         nnzb = self.nnzb()

@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
+#include <cstddef>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -202,6 +203,7 @@ bf_status step_assemble(bf_problem* pb, bool bf16) {
     ZeroList z;
     z.add(flags, 4 * 16);
     z.add(pb->viol_part.p, 4 * 2);
+    z.add(pb->scal.as<char>() + offsetof(PcgScalars, res_iters), 3 * sizeof(int));
     z.add(vcnt, 4LL * N);
     z.add(lcnt, 4LL * N);
     zero_many(z, s);
@@ -367,6 +369,7 @@ bf_status bf_context_create(int32_t device, void* hip_stream, bf_context** out) 
   int ncu = 0;
   if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && ncu > 0)
     c->num_cu = ncu;
+  c->resident_room = pcg_resident_room(c->num_cu);
   if (hip_stream) {
     c->stream = static_cast<hipStream_t>(hip_stream);
   } else {
@@ -734,7 +737,7 @@ bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* o, double* p_out, 
     if (clean) HIPCHK(c, hipGetLastError());   // of the launches so far
     SolveDevice dev{Sx, use_bf16, launched, ntime, pb->tev, s, hipSuccess};
     dev.S.hstat = pb->host_stat;
-    switch (follow_solve(dev, pb->host_stat, pcg_resident(Sx, c->num_cu))) {
+    switch (follow_solve(dev, pb->host_stat, pcg_resident(Sx, c->resident_room))) {
       case SolveEnd::kError:
         if (clean) (void)hipGetLastError();
         HIPCHK(c, dev.err);
@@ -957,6 +960,15 @@ bf_status bf_get_nnzb(bf_problem* pb, int64_t* nnzb) {
   if (!nnzb) return fail(pb->ctx, BF_ERR_INVALID_ARG, "nnzb is NULL");
   if (!pb->stepped) return fail(pb->ctx, BF_ERR_STATE, "no Newton step has been run");
   *nnzb = pb->nnzb_last;
+  return BF_OK;
+}
+
+bf_status bf_get_solver_path(bf_problem* pb, bf_solver_path* out) {
+  if (!pb) return BF_ERR_INVALID_ARG;
+  if (!out) return fail(pb->ctx, BF_ERR_INVALID_ARG, "out is NULL");
+  if (!pb->stepped) return fail(pb->ctx, BF_ERR_STATE, "no Newton step has been run");
+  const PcgScalars& h = *pb->host_sc;
+  *out = bf_solver_path{h.res_iters, h.res_launches, h.res_apart};
   return BF_OK;
 }
 

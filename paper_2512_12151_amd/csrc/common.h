@@ -73,6 +73,9 @@ struct PcgScalars {
   double rt_ref;     // |L r|^2 right after the last residual replacement (or |b|^2)
   float alpha_hist[8];   // alpha_j at j % kXBatch (written by workgroup 0 of the update kernel)
   PcgCtl ctl[2];         // state of a one-kernel solve (pcg_fused.hip), by the parity of the launch
+  // over the solves of a step: iterations and launches of the resident kernel,
+  // and how often its workgroups were not all running
+  int res_iters, res_launches, res_apart, pad;
 };
 
 // x += alpha_j p_j is applied kXBatch iterations at a time (the update kernel
@@ -421,9 +424,11 @@ int pcg_fused_groups(int N);
 hipError_t launch_pcg_fused(const PcgSystem& S, bool bf16, int par, hipStream_t s, hipEvent_t t0 = nullptr,
                             hipEvent_t t1 = nullptr);
 // The resident form: one launch that makes up to `steps` iterations of a solve
-// whose workgroups all fit the chip (pcg_resident).  It leaves the states that
-// start, resume or replace a residual to launch_pcg_fused.
-bool pcg_resident(const PcgSystem& S, int num_cu);
+// whose workgroups all fit the chip, of which it takes up to `room`
+// (pcg_resident_room).  It leaves the states that start, resume or replace a
+// residual to launch_pcg_fused.
+int pcg_resident_room(int num_cu);
+bool pcg_resident(const PcgSystem& S, int room);
 hipError_t launch_pcg_resident(const PcgSystem& S, bool bf16, int par, int steps, hipStream_t s);
 hipError_t launch_pcg_fused_batched(const PcgSystem* sys, const int* wg_sys, int nwg, int par, hipStream_t s);
 // x += the directions the update kernel has not applied yet (before x is read).

@@ -527,6 +527,11 @@ __device__ __forceinline__ bool read_totals(Buffer b, int k, int copy, int lane,
   return true;
 }
 
+// (nobody waits for it: the launch's statistics)
+__device__ __forceinline__ void count(int* n, int by) {
+  (void)__hip_atomic_fetch_add(n, by, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // A workgroup stops without having handed on a state: the host is told, and
 // the launches queued behind find both copies of the state ended.
 __device__ __forceinline__ void give_up(const PcgSystem& S) {
@@ -700,6 +705,7 @@ __device__ __forceinline__ void resident(const PcgSystem& S, PcgCtl c, int s, in
   if (!all_started(S, par)) {
     if (leader) {
       c.apart = 1;
+      count(&S.sc->res_apart, 1);
       if (S.hstat) __hip_atomic_store(&S.hstat[kWordApart], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       hand_on(S, c, par);
     }
@@ -851,6 +857,10 @@ __device__ __forceinline__ void resident(const PcgSystem& S, PcgCtl c, int s, in
   if (it > 0) {   // (all have read the sums that the launch began with)
     if (own) put32(S.x, 2u * eo, x_o);
     if (t < 5) record(S, c.k, t)[s] = mine;
+    if (leader) {
+      count(&S.sc->res_iters, it);
+      count(&S.sc->res_launches, 1);
+    }
   }
   if (leader) hand_on(S, c, par);
 }
@@ -898,10 +908,21 @@ hipError_t launch_pcg_fused(const PcgSystem& S, bool bf16, int par, hipStream_t 
                   : hipLaunchKernel(f, grid, block, args, 0, s);
 }
 
-// Two of its workgroups fit a compute unit (128 registers a thread, 47 KB of
-// LDS); a grid beyond that would never run at once.  Systems that fit gain at
-// every size (see above), so there is no other bound.
-bool pcg_resident(const PcgSystem& S, int num_cu) { return S.fused_nwg > 0 && S.fused_nwg + kCollectors <= 2 * num_cu; }
+// What the device takes at once, as the runtime works it out from the kernels'
+// registers and LDS (two to a compute unit: 128 registers a thread, 47 KB); a
+// grid beyond that would never run at once.  Systems that fit gain at every
+// size (see above), so there is no other bound.
+int pcg_resident_room(int num_cu) {
+  int a = 0, b = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&a, reinterpret_cast<const void*>(k_resident<float>), kResBlock,
+                                                   0) != hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, reinterpret_cast<const void*>(k_resident<uint32_t>), kResBlock,
+                                                   0) != hipSuccess)
+    return 0;   // (not known: by launches)
+  return num_cu * (a < b ? a : b);
+}
+
+bool pcg_resident(const PcgSystem& S, int room) { return S.fused_nwg > 0 && S.fused_nwg + kCollectors <= room; }
 
 hipError_t launch_pcg_resident(const PcgSystem& S, bool bf16, int par, int steps, hipStream_t s) {
   const void* f =

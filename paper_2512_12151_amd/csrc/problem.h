@@ -15,6 +15,7 @@ using bfal::PcgSystem;
 struct bf_context {
   int device = 0;
   int num_cu = 256;   // compute units of the device (grid sizing)
+  int resident_room = 0;   // workgroups of the resident PCG kernel that run at once
   hipStream_t stream = nullptr;
   bool own_stream = false;
   std::string err;

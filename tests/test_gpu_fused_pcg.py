@@ -205,3 +205,23 @@ def test_an_older_error_of_the_thread_is_not_the_solves():
     print("the call's error", bad, "pending before", pending, "after", after, flush=True)
     assert bad != 0 and status == status2 == 0 and np.array_equal(p, q)
     assert after == pending
+
+
+@pytest.mark.parametrize("name,make", RESIDENT, ids=[c[0] for c in RESIDENT])
+def test_the_resident_kernel_takes_what_fits_the_chip(name, make):
+    """Up to 507 slices (two workgroups to each of 256 compute units, five of
+    them collectors) most iterations are the resident kernel's; beyond, and
+    where they are timed, none are."""
+    pb = bfal.Problem.from_scene(bfal.Context(0), make())
+    opts = dict(tol=1e-9, max_iter=3000)
+    _, st, _ = pb.newton_step(**opts)
+    path = pb.solver_path()
+    print(name, st["pcg_iters"], path, flush=True)
+    assert path["apart"] == 0
+    if name == "508 slices":
+        assert path["resident_iters"] == path["resident_launches"] == 0
+    else:
+        assert path["resident_launches"] > 0
+        assert 0.5 * st["pcg_iters"] < path["resident_iters"] <= st["pcg_iters"]
+    pb.newton_step(time_spmv=4096, **opts)
+    assert pb.solver_path() == dict(resident_iters=0, resident_launches=0, apart=0)
