@@ -702,11 +702,18 @@ bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* o, double* p_out, 
   bool assembly_checked = false;
   // A one-kernel solve (follow_solve).  Sets host_sc->iter.  Where the system's
   // workgroups fit the chip the launches are, in turn, the state that starts a
-  // solve, as many steps as there are up to a replacement, and the replacement:
-  // each does nothing where the state is another's.  Launches that are timed,
-  // and a solve whose workgroups did not get the chip to themselves, take one
-  // iteration each.
-  constexpr int kResidentSteps = 4096;
+  // solve, up to kResidentSteps steps before a replacement, and the replacement:
+  // each makes one step or none where the state is another's.  Launches that
+  // are timed, and a solve whose workgroups did not get the chip to themselves,
+  // take one iteration each.
+  //
+  // A resident launch holds what it runs on, and the kernels of other streams
+  // that share its hardware queue, until it ends: 256 steps are 0.6 ms (46
+  // slices) to 1.2 ms (507), and the two launches between cost 2 % of a long
+  // solve (416 slices, 603 iterations: 3.03 ms without a bound, 3.08 with 256
+  // steps, 3.16 with 128, 3.29 with 64; without a bound a stretch of 4,096 was
+  // 18 ms).
+  constexpr int kResidentSteps = 256;
   struct SolveDevice {
     PcgSystem S;
     bool bf16;

@@ -458,7 +458,13 @@ k_fused_batched(const PcgSystem* __restrict__ sys, const int* __restrict__ wg_sy
 // instance two such grids that each got part of the chip, so the workgroups
 // first count themselves: if they are not complete within kStartTicks, one
 // marks the count, all leave without a step, and the solve goes on by
-// launches.  Once complete, every later wait ends, as each workgroup waits only
+// launches.  Ordinary kernels of other streams are waited out (a copy of 256 MB
+// takes 85 us; with 50 us instead of 100 a solve of 507 slices beside such
+// copies went on by launches, 190 a second against 275), another resident grid
+// is not worth waiting for: with 1 ms, solves of 416 slices and 41 iterations
+// took 1.39 ms each on two threads and 1.26 on four, with 100 us 0.67 and 0.70
+// (the two-kernel iteration 1.18 and 0.73; of 507 slices and 624 iterations, on
+// four threads, 3.80 and 3.11 against 3.57).  Once complete, every later wait ends, as each workgroup waits only
 // for running ones; kMaxPolls bounds it all the same.
 //
 // Measured (us per iteration, launches against this kernel): 250 nodes 6.1 ->
@@ -473,7 +479,7 @@ k_fused_batched(const PcgSystem* __restrict__ sys, const int* __restrict__ wg_sy
 constexpr int kCollectors = 5;              // workgroups, one per sum
 constexpr int kResWaves = 8;                // wavefronts per slice
 constexpr int kResBlock = kResWaves * kWave;
-constexpr long long kStartTicks = 100000;   // 1 ms of the 100 MHz clock
+constexpr long long kStartTicks = 10000;    // 100 us of the 100 MHz clock
 constexpr int kMaxPolls = 1 << 21;          // over a second
 constexpr int kSc1 = 16;                    // cache policy of the buffer accesses: sc1
 static_assert(5 * 16 <= kTotalBytes, "a line holds the totals");

@@ -225,3 +225,19 @@ def test_the_resident_kernel_takes_what_fits_the_chip(name, make):
         assert 0.5 * st["pcg_iters"] < path["resident_iters"] <= st["pcg_iters"]
     pb.newton_step(time_spmv=4096, **opts)
     assert pb.solver_path() == dict(resident_iters=0, resident_launches=0, apart=0)
+
+
+def test_a_resident_launch_is_bounded():
+    """No launch of the resident kernel makes more than 256 iterations, so that
+    other streams' kernels get their turn: a solve whose residual is not looked
+    at for 600 iterations would stay in it for all of them."""
+    sc = dict(_box(11, 15, 14))
+    sc["E"], sc["dt"] = np.full(len(sc["tets"]), 1e7), 0.1   # (stiff: some 40 iterations to a decade)
+    pb = bfal.Problem.from_scene(bfal.Context(0), sc)
+    p, st, _ = pb.newton_step(tol=1e-12, check_every=600, max_iter=600)
+    path = pb.solver_path()
+    print(st["pcg_iters"], path, flush=True)
+    assert st["pcg_iters"] == 600 and path["apart"] == 0
+    assert 0.9 * 600 < path["resident_iters"] <= 256 * path["resident_launches"]
+    q, su, _ = pb.newton_step(tol=1e-12, check_every=600, max_iter=600, time_spmv=4096)   # by launches
+    assert su["pcg_iters"] == 600 and np.array_equal(p, q)
