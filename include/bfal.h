@@ -215,7 +215,8 @@ bf_status bf_get_pattern(bf_problem* pb, int32_t* row_ptr, int32_t* col, int32_t
 bf_status bf_get_blocks(bf_problem* pb, double* vals);
 
 /* Device bytes a problem of this size holds (mesh, state, constraints,
- * pattern, blocks and solver vectors), for admission control. */
+ * pattern, blocks and solver vectors; not what the collision calls and the BF16
+ * mode add), for admission control. */
 bf_status bf_footprint_bytes(int32_t n_nodes, int32_t n_tets, int32_t n_constraints, size_t* out);
 
 /* ------------------------------------------------------------- subproblem */
@@ -325,7 +326,12 @@ typedef struct {
  * order, the new PT pairs (p, t0 < t1 < t2) ordered by (p, triangle), the
  * surviving EE constraints, the new EE pairs (a0 < a1, b0 < b1, edge a before
  * edge b) ordered by (edge a, edge b).  kappa and delta stay.  bf_energy then
- * needs a new Newton step. */
+ * needs a new Newton step.
+ *
+ * The collision calls keep, besides the trees, lists of candidate pairs on the
+ * device: 8 bytes each, at most 2^26 point-triangle and 2^26 edge-edge pairs.
+ * Where there are more, or no memory is left for a list, the query makes do
+ * without one and takes longer. */
 bf_status bf_update_active_set(bf_problem* pb, const double* x_hat, int32_t mem, double sep, bf_ccd_stats* stats);
 
 /* MaxStepSize (Algorithm 1): *alpha = min(1, the smallest collision time of

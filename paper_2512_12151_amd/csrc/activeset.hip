@@ -118,6 +118,29 @@ bf_status size_tree(bf_problem* pb, int n, const int* ids, int k, void* part, De
   return BF_OK;
 }
 
+// Candidates that the list of one kind may hold: 8 bytes each, 512 MB.  The
+// scenes here meet 3 to 20 a query; a separation offset of the size of the scene
+// makes every pair one.  Within the limit the list is much the faster way (14M
+// and 32M candidates: 9.3 ms with lists, 14.8 with the narrow phase where they
+// are found; 19M and 42M: 9.7 and 19.5); beyond it memory decides.
+constexpr long long kCandLimit = 1LL << 26;
+
+// The list of one kind with room for pb->ccap of them, or none: too many, or no memory left.
+void size_list(bf_problem* pb, int kind, int nq, QuerySide* q) {
+  if (pb->ccap[kind] == 0) pb->ccap[kind] = std::min(std::max(4096LL, 16LL * nq), kCandLimit);
+  q->cand = nullptr;
+  q->cand_cap = 0;
+  if (pb->ccap[kind] < 0) return;
+  const bool clean = hipPeekAtLastError() == hipSuccess;
+  if (pb->qcand[kind].ensure(8 * pb->ccap[kind]) != hipSuccess) {
+    if (clean) (void)hipGetLastError();   // (the error has been dealt with)
+    pb->ccap[kind] = -1;
+    return;
+  }
+  q->cand = pb->qcand[kind].as<int2>();
+  q->cand_cap = pb->ccap[kind];
+}
+
 struct Collide {
   int hits[2] = {0, 0};
   long long cand[2] = {0, 0};
@@ -158,10 +181,8 @@ bf_status collide(bf_problem* pb, const double* xh, double sep, Collide& out) {
     for (int kind = 0; kind < 2; ++kind) {
       const int nq = kind ? pb->nE : pb->nV;
       if (pb->qcap[kind] == 0) pb->qcap[kind] = std::max(4096, 4 * nq);
-      if (pb->ccap[kind] == 0) pb->ccap[kind] = std::max(4096LL, 16LL * nq);
       ALLOC(c, pb->qpairs[kind], 8LL * pb->qcap[kind]);
       ALLOC(c, pb->qtoc[kind], 8LL * pb->qcap[kind]);
-      ALLOC(c, pb->qcand[kind], 8LL * pb->ccap[kind]);
       QuerySide& q = side[kind];
       q.nq = nq;
       q.nt = kind ? pb->nE : pb->nF;
@@ -169,8 +190,7 @@ bf_status collide(bf_problem* pb, const double* xh, double sep, Collide& out) {
       q.tids = kind ? pb->sedges.as<int>() : pb->stris.as<int>();
       q.node = kind ? pb->enode.p : pb->tnode.p;
       q.key = (kind ? pb->ekey2 : pb->tkey2).as<unsigned long long>();
-      q.cand = pb->qcand[kind].as<int2>();
-      q.cand_cap = pb->ccap[kind];
+      size_list(pb, kind, nq, &q);
       q.pairs = pb->qpairs[kind].as<int2>();
       q.toc = pb->qtoc[kind].as<double>();
       q.cap = pb->qcap[kind];
@@ -188,14 +208,15 @@ bf_status collide(bf_problem* pb, const double* xh, double sep, Collide& out) {
       out.cand[kind] = cand;
       out.hits[kind] = h[8 * kind];
       todo[kind] = false;
-      if (cand > pb->ccap[kind]) {   // run this kind again with room for every candidate
-        pb->ccap[kind] = cand + cand / 4 + 1024;
+      if (side[kind].cand && cand > side[kind].cand_cap) {   // run this kind again: room for every candidate, or no list
+        pb->ccap[kind] = cand > kCandLimit ? -1 : std::min(cand + cand / 4 + 1024, kCandLimit);
         todo[kind] = true;
       }
       if (h[8 * kind] > pb->qcap[kind]) {   // ... and for every pair
         pb->qcap[kind] = h[8 * kind] + h[8 * kind] / 4 + 1024;
         todo[kind] = true;
       }
+      if (!side[kind].cand && !todo[kind] && 2 * cand <= kCandLimit) pb->ccap[kind] = 0;   // few again: a list at the next call
     }
   }
   if (todo[0] || todo[1]) return fail(c, BF_ERR_HIP, "collision pair buffer did not settle");

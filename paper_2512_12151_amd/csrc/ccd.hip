@@ -16,7 +16,8 @@
 // narrow phase made a few threads walk through all their candidates one after
 // the other while the rest of the chip was idle (a 2,300-edge scene took 515 +
 // 212 us per call in the two queries, one of 66,000 edges 645 + 343 us; the
-// split form takes 61 + 10 and 78 + 28 us).
+// split form takes 61 + 10 and 78 + 28 us).  A list is bounded (activeset.hip);
+// a kind with more candidates than that goes the old way.
 //
 // Narrow phase: additive CCD (Li, Kaufman and Jiang 2021) in FP64: remove the pair's common translation, bound the rate at which
 // the distance can shrink by l_p (largest displacement of a vertex of each
@@ -450,10 +451,42 @@ struct TraverseLds {
   int ids[2][kTraverseBlock];       // and vertices
 };
 
+// The narrow phase of one candidate.
 template <bool kEE>
+__device__ __forceinline__ void narrow(const QuerySide& q, int2 pr, const double* __restrict__ x,
+                                       const double* __restrict__ xh, double s, int* __restrict__ count) {
+  int ids[4];
+  if (kEE) {
+    ids[0] = q.qids[2LL * pr.x];
+    ids[1] = q.qids[2LL * pr.x + 1];
+    ids[2] = q.tids[2LL * pr.y];
+    ids[3] = q.tids[2LL * pr.y + 1];
+  } else {
+    ids[0] = q.qids[pr.x];
+    ids[1] = q.tids[3LL * pr.y];
+    ids[2] = q.tids[3LL * pr.y + 1];
+    ids[3] = q.tids[3LL * pr.y + 2];
+  }
+  d3 X0[4], X1[4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    X0[a] = ld3(x, ids[a]);
+    X1[a] = ld3(xh, ids[a]);
+  }
+  const double t = accd<kEE>(X0, X1, s);
+  if (t >= 0.0) {
+    const int slot = atomicAdd(count, 1);
+    if (slot < q.cap) {
+      q.pairs[slot] = pr;
+      q.toc[slot] = t;
+    }
+  }
+}
+
+template <bool kEE, bool kDirect>
 __device__ __forceinline__ void test_leaves(int n, int i0, const QuerySide& q, const double* __restrict__ x,
-                                            const double* __restrict__ xh, double delta, int* __restrict__ count,
-                                            TraverseLds& L) {
+                                            const double* __restrict__ xh, double delta, double s,
+                                            int* __restrict__ count, TraverseLds& L) {
   constexpr int kq = kEE ? 2 : 1;
   constexpr int kt = kEE ? 2 : 3;
   const int lane = threadIdx.x;
@@ -510,15 +543,19 @@ __device__ __forceinline__ void test_leaves(int n, int i0, const QuerySide& q, c
   if (lane == 0)
     base = atomicAdd(reinterpret_cast<unsigned long long*>(count + 2), (unsigned long long)kept);
   base = __shfl(base, 0, kWave);
-  for (int k = lane; k < kept; k += kWave)
-    if (base + k < (unsigned long long)q.cand_cap) q.cand[base + k] = make_int2(i0 + L.lane[k], L.leaf[k]);
+  if (kDirect && !q.cand) {
+    for (int k = lane; k < kept; k += kWave) narrow<kEE>(q, make_int2(i0 + L.lane[k], L.leaf[k]), x, xh, s, count);
+  } else {
+    for (int k = lane; k < kept; k += kWave)
+      if (base + k < (unsigned long long)q.cand_cap) q.cand[base + k] = make_int2(i0 + L.lane[k], L.leaf[k]);
+  }
   __syncthreads();
 }
 
-template <bool kEE>
+template <bool kEE, bool kDirect>
 __device__ __forceinline__ void traverse(int i0, const QuerySide& q, const double* __restrict__ x,
-                                         const double* __restrict__ xh, double delta, int* __restrict__ count,
-                                         TraverseLds& L) {
+                                         const double* __restrict__ xh, double delta, double s,
+                                         int* __restrict__ count, TraverseLds& L) {
   constexpr int kq = kEE ? 2 : 1;
   if (q.nt <= 0) return;
   const Node* __restrict__ node = static_cast<const Node*>(q.node);
@@ -566,7 +603,7 @@ __device__ __forceinline__ void traverse(int i0, const QuerySide& q, const doubl
     const bool hr = (v >= 0) & overlap(n1.z, n1.w, n2.x, n2.y, n2.z, n2.w, flo, fhi);
     const bool ll = hl & (cl >= q.nt - 1), lr = hr & (cr >= q.nt - 1);
     if (n > kLeafCap - 2 * kWave) {
-      test_leaves<kEE>(n, i0, q, x, xh, delta, count, L);
+      test_leaves<kEE, kDirect>(n, i0, q, x, xh, delta, s, count, L);
       n = 0;
     }
     meet(ll, cl - (q.nt - 1));
@@ -579,53 +616,26 @@ __device__ __forceinline__ void traverse(int i0, const QuerySide& q, const doubl
     v = a >= 0 ? a : b >= 0 ? b : sp > 0 && v >= 0 ? stack[kTraverseBlock * --sp] : -1;
   }
   if (overflow) count[1] = 1;
-  if (n) test_leaves<kEE>(n, i0, q, x, xh, delta, count, L);
+  if (n) test_leaves<kEE, kDirect>(n, i0, q, x, xh, delta, s, count, L);
 }
 
+// kDirect: a kind may come without a list; its candidates then go through the
+// narrow phase here, a wavefront's 64 at a time (activeset.hip: when, and what
+// it costs).  A kernel of its own, as the others need not hold its registers.
+template <bool kDirect>
 __global__ void __launch_bounds__(kTraverseBlock)
 k_traverse(QuerySide pt, QuerySide ee, int pt_groups, const double* __restrict__ x, const double* __restrict__ xh,
-           double delta, int* __restrict__ count) {
+           double delta, double s, int* __restrict__ count) {
   __shared__ TraverseLds L;
   const int b = blockIdx.x;
   if (b < pt_groups)
-    traverse<false>(b * kTraverseBlock, pt, x, xh, delta, count, L);
+    traverse<false, kDirect>(b * kTraverseBlock, pt, x, xh, delta, s, count, L);
   else
-    traverse<true>((b - pt_groups) * kTraverseBlock, ee, x, xh, delta, count + 8, L);
+    traverse<true, kDirect>((b - pt_groups) * kTraverseBlock, ee, x, xh, delta, s, count + 8, L);
 }
 
 // The narrow phase, one thread per candidate of either kind (grid-stride over
-// the lists, whose lengths only the device knows).
-template <bool kEE>
-__device__ __forceinline__ void narrow(const QuerySide& q, int2 pr, const double* __restrict__ x,
-                                       const double* __restrict__ xh, double s, int* __restrict__ count) {
-  int ids[4];
-  if (kEE) {
-    ids[0] = q.qids[2LL * pr.x];
-    ids[1] = q.qids[2LL * pr.x + 1];
-    ids[2] = q.tids[2LL * pr.y];
-    ids[3] = q.tids[2LL * pr.y + 1];
-  } else {
-    ids[0] = q.qids[pr.x];
-    ids[1] = q.tids[3LL * pr.y];
-    ids[2] = q.tids[3LL * pr.y + 1];
-    ids[3] = q.tids[3LL * pr.y + 2];
-  }
-  d3 X0[4], X1[4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    X0[a] = ld3(x, ids[a]);
-    X1[a] = ld3(xh, ids[a]);
-  }
-  const double t = accd<kEE>(X0, X1, s);
-  if (t >= 0.0) {
-    const int slot = atomicAdd(count, 1);
-    if (slot < q.cap) {
-      q.pairs[slot] = pr;
-      q.toc[slot] = t;
-    }
-  }
-}
-
+// the lists, whose lengths only the device knows; a kind without one has none).
 template <bool kEE>
 __device__ __forceinline__ void narrow_all(const QuerySide& q, int block, int blocks, const double* __restrict__ x,
                                            const double* __restrict__ xh, double s, int* __restrict__ count) {
@@ -978,8 +988,10 @@ size_t ccd_node_bytes(int n) { return sizeof(Node) * std::max(n - 1, 1); }
 void launch_queries(const QuerySide& pt, const QuerySide& ee, bool do_pt, bool do_ee, const double* x, const double* xh,
                     double delta, double sep, int* count, hipStream_t s) {
   const int gp = do_pt ? div_up(pt.nq, kTraverseBlock) : 0, ge = do_ee ? div_up(ee.nq, kTraverseBlock) : 0;
+  const bool direct = (do_pt && !pt.cand) || (do_ee && !ee.cand);
   if (gp + ge)
-    hipLaunchKernelGGL(k_traverse, dim3(gp + ge), dim3(kTraverseBlock), 0, s, pt, ee, gp, x, xh, delta, count);
+    hipLaunchKernelGGL(direct ? k_traverse<true> : k_traverse<false>, dim3(gp + ge), dim3(kTraverseBlock), 0, s, pt, ee,
+                       gp, x, xh, delta, sep, count);
   // 16 wavefronts per compute unit and list: the lists are walked with a stride
   const int np = gp ? 256 * 16 : 0, ne = ge ? 256 * 16 : 0;
   if (np + ne) hipLaunchKernelGGL(k_narrow, dim3(np + ne), dim3(kNarrowBlock), 0, s, pt, ee, np, x, xh, sep, count);

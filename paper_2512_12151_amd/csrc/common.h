@@ -295,7 +295,7 @@ struct QuerySide {
   const int* tids;
   const void* node;
   const unsigned long long* key;
-  int2* cand;
+  int2* cand;           // null (and no room): every candidate goes through the narrow phase where it is found
   long long cand_cap;
   int2* pairs;
   double* toc;

@@ -74,7 +74,7 @@ struct bf_problem {
   DevBuf xstart, xprev, vout;   // time step: x^t, the subproblem's input x_hat, the velocity
   int qcap[2] = {0, 0};
   DevBuf qcand[2];         // candidate pairs of the queries
-  long long ccap[2] = {0, 0};
+  long long ccap[2] = {0, 0};   // room for them (0: the first size; -1: too many for a list at the last call)
   int qhits[2] = {0, 0};   // colliding pairs of the last collision call (-1: none yet)
   bool collided = false;
   bool stepped = false;

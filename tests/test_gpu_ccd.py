@@ -285,3 +285,41 @@ def test_small_trees_match_oracle(ctx, bf, n):
     """Trees of 96 to 900 leaves: the table of node boxes has 7 to 10 levels,
     so the last launch that builds it makes one, two, three or four of them."""
     test_many_candidates_per_query_match_oracle(ctx, bf, 0.3, n)
+
+
+def test_more_candidates_than_a_list_holds(ctx, bf):
+    """With a separation offset of the size of the scene every pair of the
+    surface is a candidate: 96 and 215 million, more than the 2^26 that a list
+    holds.  Every candidate is counted and goes through the narrow phase all the
+    same, with no list, so the query takes little memory.  Only pairs that come
+    closer than a tenth of their distance collide, and no vertex moves by 0.01,
+    so the colliding pairs are those of an offset of 0.02."""
+    import torch
+    sc = dict(scenes.tiny(n=24, lateral=(0.37, 0.21)))
+    xh = scenes.ccd_target(sc, "push")
+    assert np.max(np.linalg.norm(xh - sc["x"], axis=1)) < 0.01
+    tris, edges, verts = ccd.surface(sc["tets"])
+    deg = np.bincount(edges.ravel())
+    all_pt = len(verts) * len(tris) - 3 * len(tris)
+    all_ee = len(edges) * (len(edges) - 1) // 2 - int(np.sum(deg * (deg - 1) // 2))   # (no two edges share both vertices)
+    assert min(all_pt, all_ee) > 1 << 26
+    results = []
+    pb = bf.Problem.from_scene(ctx, sc)
+    for delta in (0.02, 10.0, 0.02, 10.0):
+        pb.set_constraints(sc["pt"], sc["ee"], sc["lam"], sc["gamma"], sc["kappa"], delta)
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        alpha, st = pb.max_step_size(xh)
+        taken = before - torch.cuda.mem_get_info()[0]
+        print(f"delta {delta}: {st}, {taken / 2**20:.1f} MB taken", flush=True)
+        gpt, gtp, gee, gte = pb.collisions(st)
+        results.append((alpha, *_by_row(gpt.astype(np.int64), gtp), *_by_row(gee.astype(np.int64), gte)))
+        assert taken <= 2 * 8 * 2 ** 26 + 2 ** 26   # two lists at their largest, and the trees
+        if delta == 10.0:
+            assert (st["candidates_pt"], st["candidates_ee"]) == (all_pt, all_ee)
+    assert len(results[0][1]) > 0 and len(results[0][3]) > 0
+    for r in results[1:]:
+        assert np.array_equal(r[1], results[0][1]) and np.array_equal(r[3], results[0][3])
+        assert np.allclose(r[2], results[0][2], rtol=1e-8, atol=1e-15)
+        assert np.allclose(r[4], results[0][4], rtol=1e-8, atol=1e-15)
+        assert r[0] == pytest.approx(results[0][0], rel=1e-8)
