@@ -404,7 +404,6 @@ bf_status bf_footprint_bytes(int32_t n_nodes, int32_t n_tets, int32_t n_constrai
   b += N * 4 * 8 + C * 16 + cap * 4 * 2;           // incidence, candidates, pattern
   b += cap * (72 + 36 + 4 + 4 + 8 + 4);            // FP64 blocks, FP32 scaled blocks, ucol, eslot, transpose index, lsrc
   b += N * (12 * (4 + kPRing) + 24 + 24 + 48 + 24);   // grad, bhat, r, q, the direction ring, x, L, L^-1, p out
-  if (pcg_fused_groups(n_nodes)) b += N * 24;      // the second r and q of the one-kernel iteration
   b += 1 << 20;                                    // partials, scalars, scan scratch, the SpMV slice plan
   b += 4 * (N / 64 + 1);
   *out = b;
@@ -642,10 +641,9 @@ bf_status size_constraint_buffers(bf_problem* pb, int n_pt, int n_ee) {
   ALLOC(c, pb->xs, 24LL * N4);   // FP64 solution
   ALLOC(c, pb->rd, 24LL * N4);   // FP64 residual (replacement, refinement)
   ALLOC(c, pb->rpart, 8LL * (kMaxSpmvParts + 8 + 6 * 256 + 8));
-  const long long two = pcg_fused_groups(N) ? 2 : 1;   // the one-kernel iteration alternates between two r and q
-  ALLOC(c, pb->r, 12LL * N4 * two);
+  ALLOC(c, pb->r, 12LL * N4);
   ALLOC(c, pb->pring, 12LL * N4 * kPRing);
-  ALLOC(c, pb->q, 12LL * N4 * two);
+  ALLOC(c, pb->q, 12LL * N4);
   {
     ZeroList z;
     for (DevBuf* b : {&pb->Lf, &pb->Linv, &pb->bhat, &pb->xs, &pb->rd, &pb->r, &pb->pring, &pb->q}) z.add(b->p, b->bytes);

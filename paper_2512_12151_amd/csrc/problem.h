@@ -160,6 +160,13 @@ inline PcgSystem system_of(bf_problem* pb) {
   S.vec_nwg = pcg_vec_groups(pb->N);
   S.fused_wg0 = 0;
   S.fused_nwg = fused_groups(pb);
+  if (S.fused_nwg) {
+    // the one-kernel iteration alternates between two buffers of each vector and
+    // needs two of the ring's: its r and q lie in the ring's other ones
+    static_assert(kPRing >= 6, "p, r and q, two of each");
+    S.r = S.P + 2 * S.pstride;
+    S.q = S.P + 4 * S.pstride;
+  }
   S.bhat = pb->bhat.as<float>();
   S.aflags = pb->flags.as<int>();
   S.nnzb = pb->row_ptr.as<int>() + pb->N;

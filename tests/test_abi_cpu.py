@@ -39,3 +39,17 @@ def test_footprint_is_host_only_and_monotone():
     assert 0 < a < b
     with pytest.raises(bfal.BfalError):
         bfal.footprint_bytes(0, 10, 1)
+
+
+@pytest.mark.parametrize("tets,constraints", [(1, 0), (190000, 0), (190000, 20000)])
+def test_footprint_follows_the_sizes_alone(tets, constraints):
+    """The same bytes for every further node, also where the solver changes from
+    one iteration to another (32,768 nodes): up to the padding of the last slice
+    of 64 a footprint is an affine function of the nodes."""
+    if not os.path.exists(bfal.LIB_PATH):
+        pytest.skip("libbfal.so not built")
+    ns = [640, 16384, 32704, 32768, 32832, 40960, 400000 // 64 * 64]
+    f = [bfal.footprint_bytes(n, tets, constraints) for n in ns]
+    per = {(b - a) * 64 // (n - m) for a, b, m, n in zip(f, f[1:], ns, ns[1:])}
+    assert len(per) == 1 and min(per) > 0
+    assert all(a < b for a, b in zip(f, f[1:]))
