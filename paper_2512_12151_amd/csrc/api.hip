@@ -199,6 +199,7 @@ bf_status step_assemble(bf_problem* pb, bool bf16) {
   int npat = n;
   int* vcnt = pb->vcnt.as<int>();
   int* lcnt = pb->lcnt.as<int>();
+  HIPCHK(c, hipEventRecord(pb->ev[0], s));   // (the phases' times include their zeroing, which is here)
   {
     ZeroList z;
     z.add(flags, 4 * 16);
@@ -208,7 +209,6 @@ bf_status step_assemble(bf_problem* pb, bool bf16) {
     z.add(lcnt, 4LL * N);
     zero_many(z, s);
   }
-  HIPCHK(c, hipEventRecord(pb->ev[0], s));
   // (1) constraint linearization at x and AL factors at x_hat
   launch_contact_lin(ids, pb->n_pt, n, pb->x.as<double>(), pb->xh.as<double>(), pb->clam.as<double>(),
                      pb->cgam.as<double>(), pb->kappa, pb->delta, pb->cg.as<double>(), pb->ch.as<double>(),
