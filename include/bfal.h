@@ -181,7 +181,7 @@ bf_status bf_set_friction(bf_problem* pb, double mu_f, double eps_v);
  *
  * Systems whose workgroups fit the device at once (up to 32,448 nodes on 256
  * compute units) iterate inside one kernel, up to 256 iterations a launch.  Such
- * a launch holds its compute units for up to about 1.2 ms, and other streams'
+ * a launch holds its compute units for up to about 1.3 ms, and other streams'
  * kernels wait that long for them; solves on several streams that do not fit
  * together make one launch per iteration instead (bf_get_solver_path). */
 bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* opts, double* p_out, int32_t mem,

@@ -707,7 +707,7 @@ bf_status bf_newton_step(bf_problem* pb, const bf_solve_opts* o, double* p_out, 
   //
   // A resident launch holds what it runs on, and the kernels of other streams
   // that share its hardware queue, until it ends: 256 steps are 0.6 ms (46
-  // slices) to 1.2 ms (507), and the two launches between cost 2 % of a long
+  // slices) to 1.3 ms (507), and the two launches between cost 2 % of a long
   // solve (416 slices, 603 iterations: 3.03 ms without a bound, 3.08 with 256
   // steps, 3.16 with 128, 3.29 with 64; without a bound a stretch of 4,096 was
   // 18 ms).
