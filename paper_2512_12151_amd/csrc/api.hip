@@ -7,8 +7,8 @@
 //   -> p = L^{-T} p_hat and FP64 stats.
 #include <algorithm>
 #include <cmath>
-#include <cstdio>
 #include <cstddef>
+#include <cstdio>
 #include <cstring>
 #include <mutex>
 #include <new>

@@ -115,8 +115,8 @@ __device__ __forceinline__ void report(const PcgSystem& S, int launches, int don
     __hip_atomic_store(&S.hstat[kWordIter], (unsigned long long)(unsigned)k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __threadfence_system();
   }
-  __hip_atomic_store(&S.hstat[kWordState], ((unsigned long long)(unsigned)launches << 32) | (unsigned)done, __ATOMIC_RELAXED,
-                     __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(&S.hstat[kWordState], ((unsigned long long)(unsigned)launches << 32) | (unsigned)done,
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // The next launch's state; with an end code also the solver's scalars.
@@ -464,8 +464,9 @@ k_fused_batched(const PcgSystem* __restrict__ sys, const int* __restrict__ wg_sy
 // is not worth waiting for: with 1 ms, solves of 416 slices and 41 iterations
 // took 1.39 ms each on two threads and 1.26 on four, with 100 us 0.67 and 0.70
 // (the two-kernel iteration 1.18 and 0.73; of 507 slices and 624 iterations, on
-// four threads, 3.80 and 3.11 against 3.57).  Once complete, every later wait ends, as each workgroup waits only
-// for running ones; kMaxPolls bounds it all the same.
+// four threads, 3.80 and 3.11 against 3.57).  Once complete, every later wait
+// ends, as each workgroup waits only for running ones; kMaxPolls bounds it all
+// the same.
 //
 // Measured (us per iteration, launches against this kernel): 250 nodes 6.1 ->
 // 2.5, 2,880 nodes 6.8 -> 3.0, 24,565 nodes (slices of up to 18 slots) 9.0 ->
@@ -906,7 +907,8 @@ int pcg_fused_groups(int N) {
 }
 
 hipError_t launch_pcg_fused(const PcgSystem& S, bool bf16, int par, hipStream_t s, hipEvent_t t0, hipEvent_t t1) {
-  const void* f = bf16 ? reinterpret_cast<const void*>(k_fused<uint32_t>) : reinterpret_cast<const void*>(k_fused<float>);
+  const void* f =
+      bf16 ? reinterpret_cast<const void*>(k_fused<uint32_t>) : reinterpret_cast<const void*>(k_fused<float>);
   PcgSystem Sx = S;
   void* args[] = {&Sx, &par};
   const dim3 grid(S.fused_nwg), block(kFusedBlock);
